@@ -35,69 +35,52 @@ namespace {
 
 using namespace core;
 
-// Decode the wave's row segment; returns false if the wave has no work.
-template <int D, typename T, int L>
-__device__ __forceinline__ bool row_item(const StepArgs& a, int lane_cell, uint32_t role_off,
-                                         RowOffsets<T>& o, bool& active) {
-    // Which row segment this wave serves.  The hardware deals workgroups to
-    // the eight XCDs round-robin by id.  With xcd_rows set, workgroup b runs
-    // turn j = b / 8 on XCD b % 8, and the turns of one XCD walk whole rows
-    // (row = 8 (j / tiles_per_row) + b % 8): all segments of a row share one
-    // L2, so the cache lines that x-shifted pulls share between neighbouring
-    // segments are fetched from HBM once, while the eight XCDs together still
-    // sweep one compact band of rows.  Without it (few rows), segments go
-    // out in plain launch order.
-    const int wave = (int)(threadIdx.x >> 6);
-    int seg, row;
-    if (a.xcd_rows) {
-        const int b = (int)blockIdx.x;
-        const int j = b >> 3;
-        row = (j / a.tiles_per_row) * 8 + (b & 7);
-        seg = (j % a.tiles_per_row) * 4 + wave;
-        if (row >= a.rows || seg >= a.segs) return false;
-    } else {
-        const int item = (int)blockIdx.x * 4 + wave;
-        if (item >= a.items) return false;
-        seg = item % a.segs;
-        row = item / a.segs;
-    }
-    seg = __builtin_amdgcn_readfirstlane(seg);
-    row = __builtin_amdgcn_readfirstlane(row);
-    const int y = row % a.ny;
-    const int z = row / a.ny;
-    const int xr = seg * L + lane_cell;
-    active = xr < a.nx;
-    const int x = active ? xr : a.nx - 1;
-    fill_row_offsets<D, T>(o, x, y, z, a.nx, a.ny, a.nz, a.nxy, a.open_end, a.stream != 0,
-                           role_off);
-    return true;
+// First cell of the L cells this wave serves; false if there are none.  Waves
+// take consecutive cells whatever the row length: every store is then whole
+// 128-byte lines.  (With waves that stopped at row ends, a row that was no
+// multiple of a line made each wave write two half lines: D2Q37 FP16 on
+// 2047x1531 ran at 3.4 TB/s, D3Q107 FP16 on 191x173x187 at 2.7, and 5.3 and
+// 5.2 where rows were whole lines.  Now 273 -> 167 us and 1816 -> 987 us a
+// step there, and the same or 1-5% less on whole-line rows, where only the
+// y and z offsets have moved from scalar to vector registers.)  The
+// hardware deals workgroups to the eight XCDs round-robin by id: workgroup b
+// is turn j = b / 8 of XCD b % 8.  The turns of one XCD walk runs of a.run
+// consecutive tiles (four waves each; about one row), so that the cache lines
+// that x-shifted pulls share between neighbouring waves are fetched into one
+// L2 once, while the eight XCDs together still sweep one compact band of
+// rows.
+template <int L>
+__device__ __forceinline__ bool wave_cells(const StepArgs& a, int& first) {
+    const int b = (int)blockIdx.x, j = b >> 3;
+    const int tile = ((j / a.run) * 8 + (b & 7)) * a.run + j % a.run;
+    first = __builtin_amdgcn_readfirstlane((tile * 4 + (int)(threadIdx.x >> 6)) * L);
+    return first < (int)a.N;
 }
 
 // Fused step, one lane per cell: the lane holds all 2Q populations.  A wave
-// serves 64 cells of one row.  P is the storage precision (F64, F32Dev,
+// serves 64 consecutive cells.  P is the storage precision (F64, F32Dev,
 // F16Dev).
 template <int D, class P, int WAVES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
 void k_step(const StepArgs a) {
-    using T = typename P::T;
     using S = typename P::S;
-    constexpr int Q = VelSet<D>::Q;
-    RowOffsets<S> o;
-    bool active;
-    if (!row_item<D, S, 64>(a, (int)threadIdx.x & 63, 0u, o, active)) return;
+    int first;
+    if (!wave_cells<64>(a, first)) return;
+    // Lanes past the last cell hold that cell (clamped), loaded and updated
+    // exactly like the lane that owns it, so they store the same bits to the
+    // same place.  No branch: a branch here lets the compiler sink the whole
+    // relaxation into the store block and keep every target and population
+    // live at once.
+    const int cell = min(first + ((int)threadIdx.x & 63), (int)a.N - 1);
+    CellOffsets<D, S> o;
+    o.fill(cell, a.nx, a.ny, a.nz, a.nxy, a.open_end, a.stream != 0, 0u);
     const uint32_t plane = (uint32_t)a.P * (uint32_t)sizeof(S);
-    // Lanes past the end of a ragged row hold the row's last cell (clamped),
-    // loaded and updated exactly like the lane that owns it, so they store
-    // the same bits to the same place.  No branch: a branch here lets the
-    // compiler sink the whole relaxation into the store block and keep every
-    // target and population live at once.
-    (void)active;
     step_lane_cell<D, P>(static_cast<const char*>(a.src), static_cast<char*>(a.dst), plane, o,
                          a.ph);
 }
 
-// Fused step, split layout (see collide_split): a wave serves 32 cells of
-// one row.  This halves the registers a lane needs (Q instead of 2Q values).
+// Fused step, split layout (see collide_split): a wave serves 32
+// consecutive cells.  This halves the registers a lane needs (Q instead of 2Q values).
 template <int D, class P, int WAVES>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
 void k_step_split(const StepArgs a) {
@@ -107,16 +90,17 @@ void k_step_split(const StepArgs a) {
     const int lane = (int)threadIdx.x & 63;
     const int role = lane >> 5;  // 0: g, 1: h
     const uint32_t plane = (uint32_t)a.P * (uint32_t)sizeof(S);
-    RowOffsets<S> o;
-    bool active;
-    if (!row_item<D, S, 32>(a, lane & 31, role ? h_offset(sizeof(S), plane) : 0u, o, active))
-        return;
+    int first;
+    if (!wave_cells<32>(a, first)) return;
+    // lanes past the last cell repeat it (see k_step)
+    const int cell = min(first + (lane & 31), (int)a.N - 1);
+    CellOffsets<D, S> o;
+    o.fill(cell, a.nx, a.ny, a.nz, a.nxy, a.open_end, a.stream != 0,
+           role ? h_offset(sizeof(S), plane) : 0u);
     T p[Q];
     load_split<D, P>(static_cast<const char*>(a.src), plane, o, p, a.ph);
     collide_split<D, P>(p, role, a.ph);
-    // tail lanes store their clamped cell's identical update (see k_step)
-    (void)active;
-    store_split<D, P>(static_cast<char*>(a.dst), plane, o, p, a.ph);
+    store_split<D, P>(static_cast<char*>(a.dst), plane, o.own, p, a.ph);
 }
 
 // Fused step, split layout, with the pulled rows staged in LDS (D3Q107;
@@ -148,7 +132,7 @@ void k_step_split_lds(const StepArgs a) {
     constexpr VelSet<D> V = kVelSet<D>;
     constexpr int Q = VelSet<D>::Q;
     __shared__ __attribute__((aligned(16))) S lds[kLdsBatch * 2 * kLdsRow];
-    // workgroup b: turn j = b / 8 on XCD b % 8 walks whole rows (as row_item)
+    // workgroup b: turn j = b / 8 on XCD b % 8 walks whole rows
     const int b = (int)blockIdx.x;
     const int j = b >> 3;
     const int row = (j / a.tiles_per_row) * 8 + (b & 7);
@@ -240,10 +224,9 @@ void k_step_split_lds(const StepArgs a) {
     });
     collide_split<D, P>(p, role, a.ph);
     const uint32_t plane = (uint32_t)N * (uint32_t)sizeof(S);
-    RowOffsets<S> o;
-    o.row = (uint32_t)(y * a.nx + z * a.nxy) * cell_bytes(sizeof(S));
-    o.own = (uint32_t)(x0 + c) * cell_bytes(sizeof(S)) + (role ? h_offset(sizeof(S), plane) : 0u);
-    store_split<D, P>(static_cast<char*>(a.dst), plane, o, p, a.ph);
+    const uint32_t own = (uint32_t)(y * a.nx + z * a.nxy + x0 + c) * cell_bytes(sizeof(S)) +
+                         (role ? h_offset(sizeof(S), plane) : 0u);
+    store_split<D, P>(static_cast<char*>(a.dst), plane, own, p, a.ph);
 }
 
 // ---------------------------------------------------------------------------
@@ -343,13 +326,13 @@ void k_fd_step(const StepArgs a) {
         const int role = lane >> 5;  // 0: g, 1: h (see collide_split)
         if (!fd_item<D, S, 32>(a, lane & 31, role ? h_offset(sizeof(S), plane) : 0u, o)) return;
         T p[Q];
-        load_split<D, P, false>(src, plane, o, p, a.ph);
+        load_centre_split<D, P>(src, plane, o, p, a.ph);
         collide_split<D, P, true>(p, role, a.ph);
         convect_store_split<D, P>(src, dst, plane, o, p, a.ph);
     } else {
         if (!fd_item<D, S, 64>(a, lane, 0u, o)) return;
         T g[Q], h[Q];
-        load_lane<D, P, false>(src, plane, o, g, h, a.ph);
+        load_centre_lane<D, P>(src, plane, o, g, h, a.ph);
         collide_lane<D, P, true>(g, h, a.ph);
         convect_store_lane<D, P>(src, dst, plane, o, g, h, a.ph);
     }
@@ -465,14 +448,8 @@ __global__ __launch_bounds__(256) void k_final_reduce(const double* __restrict__
 template <int D, class P>
 hipError_t step_impl(bool split, const StepArgs& a0, hipStream_t s) {
     StepArgs a = a0;
-    const int L = split ? 32 : 64;  // cells per wave
-    a.segs = (a.nx + L - 1) / L;
-    a.rows = a.ny * a.nz;
-    a.items = a.segs * a.rows;
-    a.tiles_per_row = (a.segs + 3) / 4;  // four waves (segments) per workgroup
-    // whole rows per XCD once there are enough rows to keep all eight busy
-    a.xcd_rows = a.rows >= 64 ? 1 : 0;
-    const int grid = a.xcd_rows ? 8 * a.tiles_per_row * ((a.rows + 7) / 8) : (a.items + 3) / 4;
+    int grid;
+    step_tiles(a.N, a.nx, split ? 32 : 64, &a.run, &grid);
     // Occupancy hint for the split D3Q107 float kernels: asking for at least
     // two waves per SIMD gave 4% more bandwidth than the compiler's own
     // choice (three waves at 162 VGPRs).  In double, two waves (256 VGPRs,
@@ -494,8 +471,6 @@ hipError_t fd_step_impl(bool split, const StepArgs& a0, hipStream_t s) {
     a.segs = (a.nx + L - 1) / L;
     a.rows = a.ny * a.nz;
     a.items = a.segs * a.rows;
-    a.tiles_per_row = (a.segs + 3) / 4;
-    a.xcd_rows = 0;
     const int grid = (a.items + 3) / 4;
     if (split) return launch_kernel(&k_fd_step<D, P, true, 1>, dim3(grid), dim3(256), s, a);
     return launch_kernel(&k_fd_step<D, P, false, 1>, dim3(grid), dim3(256), s, a);
@@ -546,7 +521,15 @@ hipError_t launch_step(int dim, int precision, bool split, const StepArgs& a, hi
     });
 }
 
-int step_block_cells(int, int, bool split) { return split ? 128 : 256; }
+void step_tiles(int64_t N, int64_t nx, int wave_cells, int32_t* run, int* grid) {
+    const int64_t tile = 4 * wave_cells;
+    const int64_t tiles = (N + tile - 1) / tile;
+    // a run is about one row, as long as there are runs enough for all XCDs
+    int64_t r = (nx + tile - 1) / tile;
+    if (tiles < 64 * r) r = 1;
+    *run = (int32_t)r;
+    *grid = (int)(8 * r * ((tiles + 8 * r - 1) / (8 * r)));
+}
 
 hipError_t launch_fd_step(int dim, int precision, bool split, const StepArgs& a, hipStream_t s) {
     // no half storage in the finite-difference form (lbm_create_fd refuses it)

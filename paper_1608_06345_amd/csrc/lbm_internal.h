@@ -56,11 +56,11 @@ struct StepArgs {
     int32_t nxy;          // nx * ny
     uint32_t open_end;    // bit k: axis k is zero-gradient, else periodic
     int32_t stream;       // 1: pull-stream then collide; 0: collide in place
-    int32_t segs;         // row segments per row (one wave each)
+    int32_t run;          // lattice step: consecutive tiles an XCD serves (step_tiles)
+    int32_t segs;         // fused finite differences: row segments per row (one wave each)
     int32_t rows;         // ny * nz
     int32_t items;        // row segments in the grid
-    int32_t tiles_per_row;  // workgroups (four segments each) per row
-    int32_t xcd_rows;     // 1: each XCD serves whole rows (see kernels.hip)
+    int32_t tiles_per_row;  // row-tile kernels: tiles per row
     int32_t fd_w;         // finite-difference update sweep: tiles per x-chunk
     int32_t fd_yb;        // finite-difference update sweep: rows per y sub-band
     Physics ph;
@@ -152,7 +152,10 @@ hipError_t launch_fd_step(int dim, int precision, bool split, const StepArgs& a,
 size_t fd_record_bytes(int dim, int precision, int64_t P);
 hipError_t launch_fd_two_pass(int dim, int precision, const StepArgs& a, void* record,
                               bool record_valid, hipStream_t s);
-int step_block_cells(int dim, int precision, bool split);
+// Launch shape of a lattice step over N cells in rows of nx, with waves of
+// wave_cells cells: consecutive tiles (four waves each) an XCD serves, and
+// the grid (a multiple of 8; tiles past the last cell have no work).
+void step_tiles(int64_t N, int64_t nx, int wave_cells, int32_t* run, int* grid);
 hipError_t launch_readout(int dim, int precision, const ReadArgs& a,
                           int blocks, hipStream_t s);
 hipError_t launch_final_reduce(int dim, const double* partials, int blocks,

@@ -16,8 +16,8 @@
 //
 // A step launch has one workgroup per tile of its velocity set.  Each tile
 // belongs to one solve (binary search in the directory) and
-// covers four row segments, exactly as in a single-solve launch, including
-// the whole-rows-per-XCD order (tile starts are multiples of 8, so tile t
+// covers four waves' cells, exactly as in a single-solve launch, including
+// the order over the XCDs (tile starts are multiples of 8, so tile t
 // runs on XCD t % 8 as in a single launch).  Ping-pong parity
 // comes from the solve's own counter: it reads side steps_done & 1 and
 // writes the other.  Solves that have used up their steps are skipped.
@@ -44,7 +44,7 @@ struct SolveEntry {
     uint64_t side_bytes;
     int32_t N, P, nx, ny, nz, nxy;  // P: plane stride in cells (plane_stride)
     uint32_t open_end;
-    int32_t segs, rows, items, tiles_per_row, xcd_rows, tiles;
+    int32_t run, tiles;  // launch shape (step_tiles); tiles is a multiple of 8
     int32_t dim, active;
     int64_t steps_total;
     double omega_f, omega_g, half_delta, inv_dof;
@@ -70,21 +70,6 @@ namespace {
 
 using namespace core;
 
-
-template <int L>
-__device__ __forceinline__ bool pool_item(const SolveEntry& e, int local, int wave, int& seg,
-                                          int& row) {
-    if (e.xcd_rows) {
-        const int j = local >> 3;
-        row = (j / e.tiles_per_row) * 8 + (local & 7);
-        seg = (j % e.tiles_per_row) * 4 + wave;
-        return row < e.rows && seg < e.segs;
-    }
-    const int item = local * 4 + wave;
-    seg = item % e.segs;
-    row = item / e.segs;
-    return item < e.items;
-}
 
 // One workgroup per tile: the grid of each launch is exactly the tile count
 // of the resident solves (a loop over tiles would keep loop state live
@@ -114,18 +99,17 @@ void k_pool_step(const PoolArgs pa) {
     const SolveEntry& e = pa.table[s];
     const int64_t done = pa.steps_done[s];
     if (!e.active || done >= e.steps_total || local >= e.tiles) return;
-    int seg, row;
-    if (!pool_item<L>(e, local, wave, seg, row)) return;
-    seg = __builtin_amdgcn_readfirstlane(seg);
-    row = __builtin_amdgcn_readfirstlane(row);
-    const int y = row % e.ny;
-    const int z = row / e.ny;
-    const int xr = seg * L + (SPLIT ? (lane & 31) : lane);
-    const int x = xr < e.nx ? xr : e.nx - 1;  // tail lanes redo the last cell
+    // the solve's tiles in the order of a single launch (wave_cells, kernels.hip)
+    const int j = local >> 3;
+    const int at = ((j / e.run) * 8 + (local & 7)) * e.run + j % e.run;
+    const int first = __builtin_amdgcn_readfirstlane((at * 4 + wave) * L);
+    if (first >= e.N) return;
+    // lanes past the last cell redo it
+    const int cell = min(first + (SPLIT ? (lane & 31) : lane), e.N - 1);
     const uint32_t plane = (uint32_t)e.P * (uint32_t)sizeof(S);
-    RowOffsets<S> o;
-    fill_row_offsets<D, S>(o, x, y, z, e.nx, e.ny, e.nz, e.nxy, e.open_end, true,
-                           role ? h_offset(sizeof(S), plane) : 0u);
+    CellOffsets<D, S> o;
+    o.fill(cell, e.nx, e.ny, e.nz, e.nxy, e.open_end, true,
+           role ? h_offset(sizeof(S), plane) : 0u);
     const int par = (int)(done & 1);
     const char* src = reinterpret_cast<const char*>(e.base + (par ? e.side_bytes : 0));
     char* dst = reinterpret_cast<char*>(e.base + (par ? 0 : e.side_bytes));
@@ -138,7 +122,7 @@ void k_pool_step(const PoolArgs pa) {
         T p[Q];
         load_split<D, P>(src, plane, o, p, ph);
         collide_split<D, P>(p, role, ph);
-        store_split<D, P>(dst, plane, o, p, ph);
+        store_split<D, P>(dst, plane, o.own, p, ph);
     } else {
         step_lane_cell<D, P>(src, dst, plane, o, ph);
     }
@@ -294,17 +278,6 @@ void arena_free(lbm_pool* p, size_t off, size_t bytes) {
             p->free_list.erase(it);
         }
     }
-}
-
-int tiles_of(int dim, int precision, int64_t nx, int64_t ny, int64_t nz, SolveEntry& e) {
-    const int L = lbm::default_split(dim, precision) ? 32 : 64;  // cells per wave
-    e.segs = (int)((nx + L - 1) / L);
-    e.rows = (int)(ny * nz);
-    e.items = e.segs * e.rows;
-    e.tiles_per_row = (e.segs + 3) / 4;
-    e.xcd_rows = e.rows >= 64 ? 1 : 0;
-    const int t = e.xcd_rows ? 8 * e.tiles_per_row * ((e.rows + 7) / 8) : (e.items + 3) / 4;
-    return (t + 7) & ~7;  // tile starts stay multiples of 8
 }
 
 // Upload the table and both directories (before the next step launch).
@@ -587,7 +560,8 @@ static int pool_admit(lbm_pool_handle p, const lbm_request* r, const double* rho
     e.nz = (int32_t)r->nz;
     e.nxy = (int32_t)(r->nx * r->ny);
     e.open_end = (r->bc & 3u) | (((r->bc >> 2) & 3u) << 1) | (((r->bc >> 4) & 3u) << 2);
-    e.tiles = tiles_of(r->dim, p->precision, r->nx, r->ny, r->nz, e);
+    lbm::step_tiles(sl.N, r->nx, lbm::default_split(r->dim, p->precision) ? 32 : 64, &e.run,
+                    &e.tiles);
     e.dim = r->dim;
     e.active = 1;
     e.steps_total = r->steps;

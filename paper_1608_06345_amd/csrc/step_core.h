@@ -77,12 +77,13 @@ struct PullTable {
 };
 
 
-// Cell -> (x, y, z).
+// Cell -> (x, y, z).  Unsigned: a cell index is below 2^31 and the unsigned
+// division is the shorter one.
 __device__ __forceinline__ void coords(int cell, int nx, int nxy, int& x, int& y,
                                        int& z) {
-    z = cell / nxy;
+    z = (int)((uint32_t)cell / (uint32_t)nxy);
     const int rem = cell - z * nxy;
-    y = rem / nx;
+    y = (int)((uint32_t)rem / (uint32_t)nx);
     x = rem - y * nx;
 }
 
@@ -510,6 +511,41 @@ __device__ __forceinline__ void fill_row_offsets(RowOffsets<T>& o, int x, int y,
     o.row = (uint32_t)(y * nx + z * nxy) * cb;
 }
 
+// Pull offsets of a wave that serves consecutive cells across row ends: all
+// of them per lane.  A population load is the population's plane (scalar)
+// plus one three-operand add of lane offsets.
+template <int D, typename T>
+struct CellOffsets {
+    uint32_t xo[7], yo[7], zo[7];
+    uint32_t own;  // byte offset of the lane's own cell in a plane
+
+    __device__ __forceinline__ void fill(int cell, int nx, int ny, int nz, int nxy,
+                                         uint32_t open_end, bool stream, uint32_t role_off) {
+        constexpr uint32_t cb = cell_bytes(sizeof(T));
+        int x, y, z = 0;
+        if constexpr (D == 3) {
+            coords(cell, nx, nxy, x, y, z);
+        } else {
+            y = (int)((uint32_t)cell / (uint32_t)nx);
+            x = cell - y * nx;
+        }
+#pragma unroll
+        for (int k = 0; k < 7; ++k) {
+            const int e = stream ? k - 3 : 0;
+            xo[k] = (uint32_t)pull_coord(x, e, nx, open_end & 1u) * cb + role_off;
+            yo[k] = (uint32_t)(pull_coord(y, e, ny, open_end & 2u) * nx) * cb;
+            if constexpr (D == 3)
+                zo[k] = (uint32_t)(pull_coord(z, e, nz, open_end & 4u) * nxy) * cb;
+        }
+        own = (uint32_t)cell * cb + role_off;
+    }
+    template <int EX, int EY, int EZ>
+    __device__ __forceinline__ uint32_t src() const {
+        if constexpr (D == 3) return xo[EX + 3] + yo[EY + 3] + zo[EZ + 3];
+        else return xo[EX + 3] + yo[EY + 3];
+    }
+};
+
 // Energy-conserving collision (a mode beyond the paper).  With rates a_f,
 // a_g the BGK step changes a cell's total energy by (a_f - a_g)
 // (E_tr^eq - E_tr), E_tr = sum xi^2 g / 2 and E_tr^eq = rho (u^2 + D T) / 2,
@@ -665,70 +701,97 @@ __device__ __forceinline__ typename P::S to_store(typename P::T v, const Physics
     }
 }
 
-// PULL = false reads every population at the cell itself (the centre values
-// of the finite-difference form).
-template <int D, class P, bool PULL = true>
+template <int D, class P>
 __device__ __forceinline__ void load_lane(const char* src, uint32_t plane,
-                                          const RowOffsets<typename P::S>& o, typename P::T* g,
-                                          typename P::T* h, const Physics& ph) {
+                                          const CellOffsets<D, typename P::S>& o,
+                                          typename P::T* g, typename P::T* h,
+                                          const Physics& ph) {
     using S = typename P::S;
     constexpr VelSet<D> V = kVelSet<D>;
     static_for<0, VelSet<D>::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr Vel v = V.v[i];
-        constexpr int kx = PULL ? v.x + 3 : 3, ky = PULL ? v.y + 3 : 3, kz = PULL ? v.z + 3 : 3;
-        const char* base = src + (size_t)(2 * i) * plane + o.yo[ky] + o.zo[kz];
-        g[i] = from_store<P>(load_at<S>(base, o.xo[kx]), ph, v.group);
-        h[i] = from_store<P>(load_at<S>(base + h_offset(sizeof(S), plane), o.xo[kx]), ph, v.group);
+        const char* base = src + (size_t)(2 * i) * plane;
+        const uint32_t at = o.template src<v.x, v.y, v.z>();
+        g[i] = from_store<P>(load_at<S>(base, at), ph, v.group);
+        h[i] = from_store<P>(load_at<S>(base + h_offset(sizeof(S), plane), at), ph, v.group);
     });
 }
 
 template <int D, class P>
 __device__ __forceinline__ void store_lane(char* dst, uint32_t plane,
-                                           const RowOffsets<typename P::S>& o,
+                                           const CellOffsets<D, typename P::S>& o,
                                            const typename P::T* g, const typename P::T* h,
                                            const Physics& ph) {
     constexpr VelSet<D> V = kVelSet<D>;
-    char* row = dst + o.row;
     const uint32_t ho = h_offset(sizeof(typename P::S), plane);
     static_for<0, VelSet<D>::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr int grp = V.v[i].group;
-        char* base = row + (size_t)(2 * i) * plane;
+        char* base = dst + (size_t)(2 * i) * plane;
         store_at(base, o.own, to_store<P>(g[i], ph, grp));
         store_at(base + ho, o.own, to_store<P>(h[i], ph, grp));
     });
 }
 
 // Pull the lane's half of its cell (split layout; the role offset is in o).
-template <int D, class P, bool PULL = true>
+template <int D, class P>
 __device__ __forceinline__ void load_split(const char* src, uint32_t plane,
-                                           const RowOffsets<typename P::S>& o, typename P::T* p,
-                                           const Physics& ph) {
+                                           const CellOffsets<D, typename P::S>& o,
+                                           typename P::T* p, const Physics& ph) {
     using S = typename P::S;
     constexpr VelSet<D> V = kVelSet<D>;
     static_for<0, VelSet<D>::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         constexpr Vel v = V.v[i];
-        constexpr int kx = PULL ? v.x + 3 : 3, ky = PULL ? v.y + 3 : 3, kz = PULL ? v.z + 3 : 3;
-        const char* base = src + (size_t)(2 * i) * plane + o.yo[ky] + o.zo[kz];
-        p[i] = from_store<P>(load_at<S>(base, o.xo[kx]), ph, v.group);
+        const uint32_t at = o.template src<v.x, v.y, v.z>();
+        p[i] = from_store<P>(load_at<S>(src + (size_t)(2 * i) * plane, at), ph, v.group);
     });
 }
 
+// own: byte offset of the lane's cell (the role offset included).
 template <int D, class P>
-__device__ __forceinline__ void store_split(char* dst, uint32_t plane,
-                                            const RowOffsets<typename P::S>& o,
+__device__ __forceinline__ void store_split(char* dst, uint32_t plane, uint32_t own,
                                             const typename P::T* p, const Physics& ph) {
     constexpr VelSet<D> V = kVelSet<D>;
-    char* row = dst + o.row;
     static_for<0, VelSet<D>::Q>([&](auto I) {
         constexpr int i = decltype(I)::value;
         const auto x = to_store<P>(p[i], ph, V.v[i].group);
         if constexpr (sizeof(typename P::S) == 2)
-            store_cached(row + (size_t)(2 * i) * plane, o.own, x);
+            store_cached(dst + (size_t)(2 * i) * plane, own, x);
         else
-            store_at(row + (size_t)(2 * i) * plane, o.own, x);
+            store_at(dst + (size_t)(2 * i) * plane, own, x);
+    });
+}
+
+// The centre values of the finite-difference form: every population at the
+// cell itself.
+template <int D, class P>
+__device__ __forceinline__ void load_centre_lane(const char* src, uint32_t plane,
+                                                 const RowOffsets<typename P::S>& o,
+                                                 typename P::T* g, typename P::T* h,
+                                                 const Physics& ph) {
+    using S = typename P::S;
+    constexpr VelSet<D> V = kVelSet<D>;
+    static_for<0, VelSet<D>::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const char* base = src + (size_t)(2 * i) * plane + o.yo[3] + o.zo[3];
+        g[i] = from_store<P>(load_at<S>(base, o.xo[3]), ph, V.v[i].group);
+        h[i] = from_store<P>(load_at<S>(base + h_offset(sizeof(S), plane), o.xo[3]), ph,
+                             V.v[i].group);
+    });
+}
+
+template <int D, class P>
+__device__ __forceinline__ void load_centre_split(const char* src, uint32_t plane,
+                                                  const RowOffsets<typename P::S>& o,
+                                                  typename P::T* p, const Physics& ph) {
+    using S = typename P::S;
+    constexpr VelSet<D> V = kVelSet<D>;
+    static_for<0, VelSet<D>::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        const char* base = src + (size_t)(2 * i) * plane + o.yo[3] + o.zo[3];
+        p[i] = from_store<P>(load_at<S>(base, o.xo[3]), ph, V.v[i].group);
     });
 }
 
@@ -785,7 +848,7 @@ struct PairAcc {
 // g[] and h[] arrays, half storage as g/h words.
 template <int D, class P>
 __device__ __forceinline__ void step_lane_cell(const char* src, char* dst, uint32_t plane,
-                                               const RowOffsets<typename P::S>& o,
+                                               const CellOffsets<D, typename P::S>& o,
                                                const Physics& ph) {
     using T = typename P::T;
     constexpr int Q = VelSet<D>::Q;
@@ -795,14 +858,13 @@ __device__ __forceinline__ void step_lane_cell(const char* src, char* dst, uint3
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             constexpr Vel v = V.v[i];
-            const char* base = src + (size_t)(2 * i) * plane + o.yo[v.y + 3] + o.zo[v.z + 3];
-            w[i] = load_at<uint32_t>(base, o.xo[v.x + 3]);
+            w[i] = load_at<uint32_t>(src + (size_t)(2 * i) * plane,
+                                     o.template src<v.x, v.y, v.z>());
         });
         collide_lane_acc<D, P, false, true>(PairAcc<D>{w, ph}, ph);
-        char* row = dst + o.row;
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            store_at(row + (size_t)(2 * i) * plane, o.own, w[i]);
+            store_at(dst + (size_t)(2 * i) * plane, o.own, w[i]);
         });
     } else {
         T g[Q], h[Q];
