@@ -53,14 +53,15 @@ template <int L>
 __device__ __forceinline__ bool wave_cells(const StepArgs& a, int& first) {
     const int b = (int)blockIdx.x, j = b >> 3;
     const int tile = ((j / a.run) * 8 + (b & 7)) * a.run + j % a.run;
-    first = __builtin_amdgcn_readfirstlane((tile * 4 + (int)(threadIdx.x >> 6)) * L);
+    const int wave = tile * a.waves + (int)(threadIdx.x >> 6);
+    first = __builtin_amdgcn_readfirstlane(wave * L);
     return first < (int)a.N;
 }
 
 // Fused step, one lane per cell: the lane holds all 2Q populations.  A wave
 // serves 64 consecutive cells.  P is the storage precision (F64, F32Dev,
 // F16Dev).
-template <int D, class P, int WAVES>
+template <int D, class P, int WAVES, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
 void k_step(const StepArgs a) {
     using S = typename P::S;
@@ -73,15 +74,15 @@ void k_step(const StepArgs a) {
     // live at once.
     const int cell = min(first + ((int)threadIdx.x & 63), (int)a.N - 1);
     CellOffsets<D, S> o;
-    o.fill(cell, a.nx, a.ny, a.nz, a.nxy, a.open_end, a.stream != 0, 0u);
+    o.fill(cell, a.nx, a.ny, a.nz, a.nxy, a.pull, 0u);
     const uint32_t plane = (uint32_t)a.P * (uint32_t)sizeof(S);
-    step_lane_cell<D, P>(static_cast<const char*>(a.src), static_cast<char*>(a.dst), plane, o,
+    step_lane_cell<D, P, NT>(static_cast<const char*>(a.src), static_cast<char*>(a.dst), plane, o,
                          a.ph);
 }
 
 // Fused step, split layout (see collide_split): a wave serves 32
 // consecutive cells.  This halves the registers a lane needs (Q instead of 2Q values).
-template <int D, class P, int WAVES>
+template <int D, class P, int WAVES, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
 void k_step_split(const StepArgs a) {
     using T = typename P::T;
@@ -95,12 +96,11 @@ void k_step_split(const StepArgs a) {
     // lanes past the last cell repeat it (see k_step)
     const int cell = min(first + (lane & 31), (int)a.N - 1);
     CellOffsets<D, S> o;
-    o.fill(cell, a.nx, a.ny, a.nz, a.nxy, a.open_end, a.stream != 0,
-           role ? h_offset(sizeof(S), plane) : 0u);
+    o.fill(cell, a.nx, a.ny, a.nz, a.nxy, a.pull, role ? h_offset(sizeof(S), plane) : 0u);
     T p[Q];
     load_split<D, P>(static_cast<const char*>(a.src), plane, o, p, a.ph);
     collide_split<D, P>(p, role, a.ph);
-    store_split<D, P>(static_cast<char*>(a.dst), plane, o.own, p, a.ph);
+    store_split<D, P, NT>(static_cast<char*>(a.dst), plane, o.own, p, a.ph);
 }
 
 // Fused step, split layout, with the pulled rows staged in LDS (D3Q107;
@@ -226,7 +226,7 @@ void k_step_split_lds(const StepArgs a) {
     const uint32_t plane = (uint32_t)N * (uint32_t)sizeof(S);
     const uint32_t own = (uint32_t)(y * a.nx + z * a.nxy + x0 + c) * cell_bytes(sizeof(S)) +
                          (role ? h_offset(sizeof(S), plane) : 0u);
-    store_split<D, P>(static_cast<char*>(a.dst), plane, own, p, a.ph);
+    store_split<D, P, true>(static_cast<char*>(a.dst), plane, own, p, a.ph);
 }
 
 // ---------------------------------------------------------------------------
@@ -448,8 +448,15 @@ __global__ __launch_bounds__(256) void k_final_reduce(const double* __restrict__
 template <int D, class P>
 hipError_t step_impl(bool split, const StepArgs& a0, hipStream_t s) {
     StepArgs a = a0;
+    a.pull = pull_grid(a.nx, a.ny, a.nz, a.open_end, a.stream != 0);
+    const int L = split ? 32 : 64;  // cells per wave
+    // Up to one wave for each SIMD of the chip: workgroups of one wave, which
+    // spread over all CUs (us a step, four waves / one: D3Q107 FP64 on 23x9x16,
+    // 104 waves, 13.5 / 9.2, D2Q37 FP64 200x4 8.2 / 5.1, 1000x16 9.8 / 7.8).
+    a.waves = (a.N + L - 1) / L <= 1024 ? 1 : 4;
     int grid;
-    step_tiles(a.N, a.nx, split ? 32 : 64, &a.run, &grid);
+    step_tiles(a.N, a.nx, a.waves * L, &a.run, &grid);
+    const dim3 block(64 * a.waves);
     // Occupancy hint for the split D3Q107 float kernels: asking for at least
     // two waves per SIMD gave 4% more bandwidth than the compiler's own
     // choice (three waves at 162 VGPRs).  In double, two waves (256 VGPRs,
@@ -458,10 +465,17 @@ hipError_t step_impl(bool split, const StepArgs& a0, hipStream_t s) {
     // spills added 13% to the HBM bytes; it keeps one.  The other kernels
     // run best as compiled.
     constexpr int kSplitWaves = (D == 3 && sizeof(typename P::T) == 4) ? 2 : 1;
-    if (split)
-        return launch_kernel(&k_step_split<D, P, kSplitWaves>, dim3(grid), dim3(256), s, a);
-    else
-        return launch_kernel(&k_step<D, P, 1>, dim3(grid), dim3(256), s, a);
+    // Stores (streamed / cached, us a step): D2Q37 FP32 512^2 (155 MB) 33.0 /
+    // 25.1, 700^2 (290 MB) 57.0 / 53.0, FP16 1024^2 (310 MB) 70.6 / 66.9, D3Q107
+    // FP32 45x40x40 (123 MB) 30.8 / 25.3; beyond, D3Q107 FP32 64^3 (449 MB)
+    // 87.0 / 88.8, 256^3 5149 / 5715; below, FP32 32^3 (56 MB) 13.4 / 14.3, D2Q37
+    // 256^2 (39 MB) 11.5 / 11.9.
+    const int64_t state = state_bytes(D, sizeof(typename P::S), a.P);
+    const bool nt = state <= (int64_t(64) << 20) || state > (int64_t(304) << 20);
+    auto* kernel = split ? (nt ? &k_step_split<D, P, kSplitWaves, true>
+                               : &k_step_split<D, P, kSplitWaves, false>)
+                         : (nt ? &k_step<D, P, 1, true> : &k_step<D, P, 1, false>);
+    return launch_kernel(kernel, dim3(grid), block, s, a);
 }
 
 template <int D, class P>
@@ -521,8 +535,7 @@ hipError_t launch_step(int dim, int precision, bool split, const StepArgs& a, hi
     });
 }
 
-void step_tiles(int64_t N, int64_t nx, int wave_cells, int32_t* run, int* grid) {
-    const int64_t tile = 4 * wave_cells;
+void step_tiles(int64_t N, int64_t nx, int tile, int32_t* run, int* grid) {
     const int64_t tiles = (N + tile - 1) / tile;
     // a run is about one row, as long as there are runs enough for all XCDs
     int64_t r = (nx + tile - 1) / tile;

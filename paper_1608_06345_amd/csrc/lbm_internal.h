@@ -45,6 +45,44 @@ struct Physics {
     float ecf;                // the same, rounded to float
 };
 
+// Division of 0 <= n < 2^31 by a divisor d >= 1 known to the host: with l =
+// ceil(log2 d) and mul = ceil(2^(31 + l) / d) < 2^32, n mul / 2^(31 + l) exceeds
+// n / d by less than 1 / d, so that (2 n mul) >> (32 + l) is the quotient.
+struct Divisor {
+    uint32_t mul, shift;
+};
+inline Divisor divisor_of(int64_t d) {
+    uint32_t l = 0;
+    while ((int64_t(1) << l) < d) ++l;
+    const uint64_t p = uint64_t(1) << (31 + l);
+    return {(uint32_t)((p + (uint64_t)d - 1) / (uint64_t)d), l};
+}
+
+// Where a pull reads along one axis of n cells: e = 1, 2, 3 cells away, taken
+// modulo n on a periodic axis (and 0 without streaming), one turn of n (none
+// at open ends) bringing it back.
+struct PullAxis {
+    int32_t turn;
+    int32_t shift[3];
+};
+struct PullGrid {
+    PullAxis axis[3];
+    Divisor by_nx, by_nxy;
+};
+inline PullGrid pull_grid(int64_t nx, int64_t ny, int64_t nz, uint32_t open_end, bool stream) {
+    PullGrid g;
+    const int64_t n[3] = {nx, ny, nz};
+    for (int k = 0; k < 3; ++k) {
+        const bool open = open_end >> k & 1u;
+        g.axis[k].turn = open ? 0 : (int32_t)n[k];
+        for (int e = 1; e <= 3; ++e)
+            g.axis[k].shift[e - 1] = !stream ? 0 : (open ? e : (int32_t)(e % n[k]));
+    }
+    g.by_nx = divisor_of(nx);
+    g.by_nxy = divisor_of(nx * ny);
+    return g;
+}
+
 // Arguments of the fused step kernel (passed by value in the kernarg
 // segment, so every field is wave-uniform and lives in SGPRs).
 struct StepArgs {
@@ -56,13 +94,17 @@ struct StepArgs {
     int32_t nxy;          // nx * ny
     uint32_t open_end;    // bit k: axis k is zero-gradient, else periodic
     int32_t stream;       // 1: pull-stream then collide; 0: collide in place
-    int32_t run;          // lattice step: consecutive tiles an XCD serves (step_tiles)
+    PullGrid pull;        // lattice step
+    int32_t run;          // consecutive tiles an XCD serves (step_tiles)
+    int32_t waves;        // waves per workgroup (tile)
     int32_t segs;         // fused finite differences: row segments per row (one wave each)
     int32_t rows;         // ny * nz
     int32_t items;        // row segments in the grid
     int32_t tiles_per_row;  // row-tile kernels: tiles per row
     int32_t fd_w;         // finite-difference update sweep: tiles per x-chunk
     int32_t fd_yb;        // finite-difference update sweep: rows per y sub-band
+    int32_t fd_tx, fd_ty, fd_tz;  // finite-difference update: tiles per axis
+    int32_t fd_bw, fd_bh, fd_bd;  // and per brick (fd.hip)
     Physics ph;
 };
 
@@ -80,6 +122,14 @@ int64_t plane_stride(int64_t N, size_t elem, int dim);
 constexpr uint32_t cell_bytes(size_t elem) { return elem == 2 ? 4u : (uint32_t)elem; }
 constexpr uint32_t h_offset(size_t elem, uint32_t plane_bytes) {
     return elem == 2 ? 2u : plane_bytes;
+}
+
+// Bytes of both sides of a state together.  A step's stores stream past the
+// caches unless that much fits the 256 MiB last-level cache (about, and by
+// far not the L2s): then a cached store leaves the state there for the next
+// step's reads.
+constexpr int64_t state_bytes(int dim, size_t elem, int64_t P) {
+    return 4 * (dim == 2 ? 37 : 107) * (int64_t)elem * P;
 }
 
 // Register layout the lattice step takes by default.  D3Q107 in float or
@@ -152,10 +202,10 @@ hipError_t launch_fd_step(int dim, int precision, bool split, const StepArgs& a,
 size_t fd_record_bytes(int dim, int precision, int64_t P);
 hipError_t launch_fd_two_pass(int dim, int precision, const StepArgs& a, void* record,
                               bool record_valid, hipStream_t s);
-// Launch shape of a lattice step over N cells in rows of nx, with waves of
-// wave_cells cells: consecutive tiles (four waves each) an XCD serves, and
-// the grid (a multiple of 8; tiles past the last cell have no work).
-void step_tiles(int64_t N, int64_t nx, int wave_cells, int32_t* run, int* grid);
+// Launch shape of a lattice step over N cells in rows of nx, with workgroups
+// of `tile` cells: consecutive tiles an XCD serves, and the grid (a multiple
+// of 8; tiles past the last cell have no work).
+void step_tiles(int64_t N, int64_t nx, int tile, int32_t* run, int* grid);
 hipError_t launch_readout(int dim, int precision, const ReadArgs& a,
                           int blocks, hipStream_t s);
 hipError_t launch_final_reduce(int dim, const double* partials, int blocks,

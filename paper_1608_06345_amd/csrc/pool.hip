@@ -44,6 +44,7 @@ struct SolveEntry {
     uint64_t side_bytes;
     int32_t N, P, nx, ny, nz, nxy;  // P: plane stride in cells (plane_stride)
     uint32_t open_end;
+    PullGrid pull;
     int32_t run, tiles;  // launch shape (step_tiles); tiles is a multiple of 8
     int32_t dim, active;
     int64_t steps_total;
@@ -108,8 +109,7 @@ void k_pool_step(const PoolArgs pa) {
     const int cell = min(first + (SPLIT ? (lane & 31) : lane), e.N - 1);
     const uint32_t plane = (uint32_t)e.P * (uint32_t)sizeof(S);
     CellOffsets<D, S> o;
-    o.fill(cell, e.nx, e.ny, e.nz, e.nxy, e.open_end, true,
-           role ? h_offset(sizeof(S), plane) : 0u);
+    o.fill(cell, e.nx, e.ny, e.nz, e.nxy, e.pull, role ? h_offset(sizeof(S), plane) : 0u);
     const int par = (int)(done & 1);
     const char* src = reinterpret_cast<const char*>(e.base + (par ? e.side_bytes : 0));
     char* dst = reinterpret_cast<char*>(e.base + (par ? 0 : e.side_bytes));
@@ -122,9 +122,9 @@ void k_pool_step(const PoolArgs pa) {
         T p[Q];
         load_split<D, P>(src, plane, o, p, ph);
         collide_split<D, P>(p, role, ph);
-        store_split<D, P>(dst, plane, o.own, p, ph);
+        store_split<D, P, true>(dst, plane, o.own, p, ph);
     } else {
-        step_lane_cell<D, P>(src, dst, plane, o, ph);
+        step_lane_cell<D, P, true>(src, dst, plane, o, ph);
     }
 }
 
@@ -560,7 +560,8 @@ static int pool_admit(lbm_pool_handle p, const lbm_request* r, const double* rho
     e.nz = (int32_t)r->nz;
     e.nxy = (int32_t)(r->nx * r->ny);
     e.open_end = (r->bc & 3u) | (((r->bc >> 2) & 3u) << 1) | (((r->bc >> 4) & 3u) << 2);
-    lbm::step_tiles(sl.N, r->nx, lbm::default_split(r->dim, p->precision) ? 32 : 64, &e.run,
+    e.pull = lbm::pull_grid(e.nx, e.ny, e.nz, e.open_end, true);
+    lbm::step_tiles(sl.N, r->nx, lbm::default_split(r->dim, p->precision) ? 128 : 256, &e.run,
                     &e.tiles);
     e.dim = r->dim;
     e.active = 1;

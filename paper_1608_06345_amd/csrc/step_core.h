@@ -43,6 +43,13 @@ __device__ __forceinline__ void store_cached(char* base, uint32_t byte_off, T v)
     *reinterpret_cast<T*>(base + byte_off) = v;
 }
 
+// NT: past the caches, as above (see state_bytes).
+template <bool NT, typename T>
+__device__ __forceinline__ void store_as(char* base, uint32_t byte_off, T v) {
+    if constexpr (NT) store_at(base, byte_off, v);
+    else store_cached(base, byte_off, v);
+}
+
 // Source coordinate of a pull along one axis: x - e, wrapped (periodic) or
 // clamped (zero gradient).
 __device__ __forceinline__ int pull_coord(int x, int e, int n, bool open_end) {
@@ -76,6 +83,11 @@ struct PullTable {
     }
 };
 
+
+// n / d for 0 <= n < 2^31 (see Divisor).
+__device__ __forceinline__ int divide(int n, Divisor d) {
+    return (int)(__umulhi((uint32_t)n << 1, d.mul) >> d.shift);
+}
 
 // Cell -> (x, y, z).  Unsigned: a cell index is below 2^31 and the unsigned
 // division is the shorter one.
@@ -519,24 +531,39 @@ struct CellOffsets {
     uint32_t xo[7], yo[7], zo[7];
     uint32_t own;  // byte offset of the lane's own cell in a plane
 
-    __device__ __forceinline__ void fill(int cell, int nx, int ny, int nz, int nxy,
-                                         uint32_t open_end, bool stream, uint32_t role_off) {
-        constexpr uint32_t cb = cell_bytes(sizeof(T));
-        int x, y, z = 0;
-        if constexpr (D == 3) {
-            coords(cell, nx, nxy, x, y, z);
-        } else {
-            y = (int)((uint32_t)cell / (uint32_t)nx);
-            x = cell - y * nx;
-        }
+    // One axis' byte offsets for shifts e = k - 3 = -3..3 at position pos.  No
+    // branches and no division: on small grids the way to the first load is a
+    // good part of a launch (D3Q107 FP32, 23x9x16: 10.8 us a step with the
+    // wrap chosen by branches and coordinates by division, 9.9 so).
+    __device__ __forceinline__ static void axis(uint32_t* o, int pos, const PullAxis& a, int n,
+                                                uint32_t stride) {
+        o[3] = (uint32_t)pos * stride;
 #pragma unroll
-        for (int k = 0; k < 7; ++k) {
-            const int e = stream ? k - 3 : 0;
-            xo[k] = (uint32_t)pull_coord(x, e, nx, open_end & 1u) * cb + role_off;
-            yo[k] = (uint32_t)(pull_coord(y, e, ny, open_end & 2u) * nx) * cb;
-            if constexpr (D == 3)
-                zo[k] = (uint32_t)(pull_coord(z, e, nz, open_end & 4u) * nxy) * cb;
+        for (int e = 1; e <= 3; ++e) {
+            // pos - e: below 0 one turn up (as unsigned numbers the smaller
+            // of both is the one in the grid), or 0 at an open end; pos + e
+            // likewise
+            const uint32_t lo = (uint32_t)(pos - a.shift[e - 1]);
+            o[3 + e] = (uint32_t)max((int)min(lo, lo + (uint32_t)a.turn), 0) * stride;
+            const uint32_t hi = (uint32_t)(pos + a.shift[e - 1]);
+            o[3 - e] = (uint32_t)min((int)min(hi, hi - (uint32_t)a.turn), n - 1) * stride;
         }
+    }
+    __device__ __forceinline__ void fill(int cell, int nx, int ny, int nz, int nxy,
+                                         const PullGrid& g, uint32_t role_off) {
+        constexpr uint32_t cb = cell_bytes(sizeof(T));
+        int z = 0, rem = cell;
+        if constexpr (D == 3) {
+            z = divide(cell, g.by_nxy);
+            rem = cell - z * nxy;
+            axis(zo, z, g.axis[2], nz, (uint32_t)nxy * cb);
+        }
+        const int y = divide(rem, g.by_nx);
+        const int x = rem - y * nx;
+        axis(yo, y, g.axis[1], ny, (uint32_t)nx * cb);
+        axis(xo, x, g.axis[0], nx, cb);
+#pragma unroll
+        for (int k = 0; k < 7; ++k) xo[k] += role_off;
         own = (uint32_t)cell * cb + role_off;
     }
     template <int EX, int EY, int EZ>
@@ -718,7 +745,7 @@ __device__ __forceinline__ void load_lane(const char* src, uint32_t plane,
     });
 }
 
-template <int D, class P>
+template <int D, class P, bool NT>
 __device__ __forceinline__ void store_lane(char* dst, uint32_t plane,
                                            const CellOffsets<D, typename P::S>& o,
                                            const typename P::T* g, const typename P::T* h,
@@ -729,8 +756,8 @@ __device__ __forceinline__ void store_lane(char* dst, uint32_t plane,
         constexpr int i = decltype(I)::value;
         constexpr int grp = V.v[i].group;
         char* base = dst + (size_t)(2 * i) * plane;
-        store_at(base, o.own, to_store<P>(g[i], ph, grp));
-        store_at(base + ho, o.own, to_store<P>(h[i], ph, grp));
+        store_as<NT>(base, o.own, to_store<P>(g[i], ph, grp));
+        store_as<NT>(base + ho, o.own, to_store<P>(h[i], ph, grp));
     });
 }
 
@@ -750,7 +777,7 @@ __device__ __forceinline__ void load_split(const char* src, uint32_t plane,
 }
 
 // own: byte offset of the lane's cell (the role offset included).
-template <int D, class P>
+template <int D, class P, bool NT>
 __device__ __forceinline__ void store_split(char* dst, uint32_t plane, uint32_t own,
                                             const typename P::T* p, const Physics& ph) {
     constexpr VelSet<D> V = kVelSet<D>;
@@ -760,7 +787,7 @@ __device__ __forceinline__ void store_split(char* dst, uint32_t plane, uint32_t 
         if constexpr (sizeof(typename P::S) == 2)
             store_cached(dst + (size_t)(2 * i) * plane, own, x);
         else
-            store_at(dst + (size_t)(2 * i) * plane, own, x);
+            store_as<NT>(dst + (size_t)(2 * i) * plane, own, x);
     });
 }
 
@@ -846,7 +873,7 @@ struct PairAcc {
 
 // Pull, collide and store one cell in the lane layout: F64 and F32Dev as
 // g[] and h[] arrays, half storage as g/h words.
-template <int D, class P>
+template <int D, class P, bool NT>
 __device__ __forceinline__ void step_lane_cell(const char* src, char* dst, uint32_t plane,
                                                const CellOffsets<D, typename P::S>& o,
                                                const Physics& ph) {
@@ -864,13 +891,13 @@ __device__ __forceinline__ void step_lane_cell(const char* src, char* dst, uint3
         collide_lane_acc<D, P, false, true>(PairAcc<D>{w, ph}, ph);
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
-            store_at(dst + (size_t)(2 * i) * plane, o.own, w[i]);
+            store_as<NT>(dst + (size_t)(2 * i) * plane, o.own, w[i]);
         });
     } else {
         T g[Q], h[Q];
         load_lane<D, P>(src, plane, o, g, h, ph);
         collide_lane<D, P>(g, h, ph);
-        store_lane<D, P>(dst, plane, o, g, h, ph);
+        store_lane<D, P, NT>(dst, plane, o, g, h, ph);
     }
 }
 
