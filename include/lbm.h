@@ -167,10 +167,10 @@ int lbm_set_stream(lbm_handle h, void *stream);
  *   SPLIT     fused kernel, a lane pair holds them, g in lane l and h in
  *             lane l + 32 of the wave;
  *   TWO_PASS  (lbm_create_fd solves only) the finite-difference step as a
- *             moments pass plus updates of chunks of populations, which
- *             keeps each chunk's neighbour rows in cache; where nx is a
- *             multiple of 256 the updates stage each population's stencil
- *             rows in LDS (same results to rounding);
+ *             per-cell record of the macroscopic state and updates of the
+ *             populations from it: in FP64 on grids of some size one launch
+ *             that walks tiles of cells through all planes in LDS, else a
+ *             launch per chunk of populations (same results to rounding);
  *   SPLIT_LDS (D3Q107 lattice streaming, nx a multiple of 128) SPLIT with
  *             the pulled rows staged in LDS: a workgroup loads each
  *             population's shifted row once, four cells a lane, and each
@@ -179,9 +179,8 @@ int lbm_set_stream(lbm_handle h, void *stream);
  *   AUTO      (the default) lattice streaming: LANE for D2Q37 and for half
  *             storage, SPLIT for D3Q107 in FP64 and FP32, whose 214
  *             populations do not fit one lane's registers; finite
- *             differences: TWO_PASS, except LANE for
- *             D2Q37 in FP64 when nx is not a multiple of 256, where the
- *             fused kernel is faster than the two-pass step without LDS.
+ *             differences: TWO_PASS, except LANE for D2Q37 in FP64 on
+ *             grids under 25000 cells whose nx is not a multiple of 256.
  * EINVAL for other values, for TWO_PASS on a lattice-streaming solve, and for
  * SPLIT_LDS on any other solve. */
 enum lbm_variant {

@@ -144,15 +144,12 @@ int lbm::solver_readout(lbm_solver* h, double* rho, double* u, double* E, double
 
 namespace {
 
-// Finite differences, AUTO variant: the two-pass step, except for D2Q37 in
-// FP64 on rows that are not whole 256-cell tiles.  There the fused kernel's
-// neighbour rows still fit the L2 and it streams faster than the two-pass
-// step with its one-lane update kernel (measured on 4096^2: 5.9 ms fused,
-// 8.7 ms two-pass with that kernel); with the LDS-staged update the
-// two-pass step is faster (5.4-5.6 ms).  D3Q107 FP32 256^3: 31.7 ms fused,
-// 10.2 ms two-pass.
-bool fd_fused_by_default(int dim, int precision, int64_t nx) {
-    return dim == 2 && precision == LBM_FP64 && nx % 256 != 0;
+// Finite differences, AUTO variant: the step from a record (fd.hip), except
+// for D2Q37 in FP64 on the smallest grids, where one fused launch is done
+// before two (1000x16, 128 kB a plane: 21.5 us fused, 22.4 in two; 256x128,
+// 262 kB: 23.6 and 22.6).
+bool fd_fused_by_default(int dim, int precision, int64_t nx, int64_t N) {
+    return dim == 2 && precision == LBM_FP64 && nx % 256 != 0 && N * 8 < 200000;
 }
 
 }  // namespace
@@ -272,7 +269,7 @@ int create_solver(int dim, int velocity_set, double gamma, double tau_f, double 
     // across lane pairs (half storage holds them as 107 g/h words)
     h->split = lbm::default_split(dim, precision);
     h->lds = false;
-    h->fd_fused = fd_fused_by_default(dim, precision, nx);
+    h->fd_fused = fd_fused_by_default(dim, precision, nx, s.N);
     hipError_t e = hipGetDevice(&h->device);
     if (e != hipSuccess) {
         delete h;
@@ -330,7 +327,7 @@ int lbm_set_variant(lbm_handle h, int variant) {
     switch (variant) {
         case LBM_VARIANT_AUTO:
             h->split = lbm::default_split(h->dim, h->precision);
-            h->fd_fused = fd_fused_by_default(h->dim, h->precision, h->nx);
+            h->fd_fused = fd_fused_by_default(h->dim, h->precision, h->nx, h->N);
             h->lds = false;
             return LBM_OK;
         case LBM_VARIANT_LANE:
