@@ -77,7 +77,7 @@ size_t footprint(const Shape& s) {
     return 2 * side + partial + 8 * sizeof(double);
 }
 
-lbm::StepArgs step_args(const lbm_solver* h, const void* src, void* dst, bool stream) {
+lbm::StepArgs step_args(const lbm_solver* h, const void* src, void* dst) {
     lbm::StepArgs a;
     std::memset(&a, 0, sizeof(a));
     a.src = src;
@@ -89,7 +89,6 @@ lbm::StepArgs step_args(const lbm_solver* h, const void* src, void* dst, bool st
     a.nz = (int32_t)h->nz;
     a.nxy = (int32_t)(h->nx * h->ny);
     a.open_end = (h->bc & 3u) | (((h->bc >> 2) & 3u) << 1) | (((h->bc >> 4) & 3u) << 2);
-    a.stream = stream ? 1 : 0;
     a.ph = lbm::physics_of(h->dim, h->delta, h->tau_f, h->tau_g, h->scheme ? h->dt : 0.0,
                            h->collision == LBM_COLLISION_ENERGY_CONSERVING);
     return a;
@@ -373,11 +372,9 @@ int lbm_synchronize(lbm_handle h) {
 
 int lbm_init_fields_dev(lbm_handle h, const double* rho, const double* u, const double* T) {
     if (!h || !rho || !u || !T) return LBM_EINVAL;
-    // S_0 into side 0; P_0 = Collide(S_0) into side 1 (same collision code as
-    // every step, with the pull switched off).
-    LBM_HIP(lbm::launch_init(h->dim, h->precision, h->buf[0], rho, u, T, h->N, h->P,
-                             0.5 * h->delta, h->lat->r, h->lat->w_group, h->stream));
+    const lbm::InitFields f{rho, u, T, h->N, h->P, 0.5 * h->delta, h->lat->r};
     if (h->scheme) {  // finite differences keep S_n itself
+        LBM_HIP(lbm::launch_init(h->dim, h->precision, h->buf[0], f, h->lat->w_group, h->stream));
         h->fd_record_valid = false;
         h->cur = 0;
         h->initial = true;
@@ -385,8 +382,11 @@ int lbm_init_fields_dev(lbm_handle h, const double* rho, const double* u, const 
         h->steps = 0;
         return LBM_OK;
     }
-    const lbm::StepArgs a = step_args(h, h->buf[0], h->buf[1], false);
-    LBM_HIP(lbm::launch_step(h->dim, h->precision, h->split, a, h->stream));
+    // S_0 into side 0; P_0 = Collide(S_0) into side 1 (same collision code as
+    // every step)
+    const lbm::StepArgs a = step_args(h, nullptr, nullptr);
+    LBM_HIP(lbm::launch_init_collide(h->dim, h->precision, h->split, h->buf[0], h->buf[1], f, a.ph,
+                                     h->lat->w_group, h->stream));
     h->cur = 1;
     h->initial = true;
     h->have_state = true;
@@ -415,7 +415,7 @@ int lbm_step(lbm_handle h, int64_t n) {
     if (!h || n < 0) return LBM_EINVAL;
     if (!h->have_state) return LBM_ESTATE;
     for (int64_t k = 0; k < n; ++k) {
-        const lbm::StepArgs a = step_args(h, h->buf[h->cur], h->buf[h->cur ^ 1], true);
+        const lbm::StepArgs a = step_args(h, h->buf[h->cur], h->buf[h->cur ^ 1]);
         if (h->scheme && h->fd_fused) {
             LBM_HIP(lbm::launch_fd_step(h->dim, h->precision, h->split, a, h->stream));
             h->fd_record_valid = false;

@@ -233,35 +233,47 @@ void k_step_split_lds(const StepArgs a) {
 // Initial state S_0 = equilibrium of (rho, u, T), evaluated in double and
 // stored in the storage precision (deviation from the rest equilibrium in
 // FP32_DEV: g_i - w_i, h_i - (delta/2) w_i).
-template <int D, class P>
-__global__ __launch_bounds__(256) void k_init(char* dst, const double* __restrict__ rho_in,
-                                              const double* __restrict__ u_in,
-                                              const double* __restrict__ T_in, int64_t N,
-                                              int64_t stride, double half_delta, double r,
-                                              const WGroups wg) {
-    constexpr VelSet<D> V = kVelSet<D>;
-    constexpr int Q = VelSet<D>::Q;
-    const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (cell >= N) return;
-    const double rho = rho_in[cell];
-    const double temp = T_in[cell];
-    double u[3] = {0, 0, 0};
-#pragma unroll
-    for (int k = 0; k < D; ++k) u[k] = u_in[k * N + cell];
+//
+// x / w, with 1 / w (rounded once) at hand: the first quotient is within an
+// ulp, its remainder exact, and the corrected one is x / w rounded once
+// (Markstein's division).  A remainder that is not a number leaves the first.
+__device__ __forceinline__ double quotient(double x, double w, double inv_w) {
+#pragma clang fp contract(off)
+    const double q = x * inv_w;
+    const double r = __builtin_fma(-q, w, x);
+    return r == r ? __builtin_fma(r, inv_w, q) : q;
+}
+
+template <int D>
+struct InitCell {
     Equilibrium<D, double, true> eq;  // deviation form, in double
-    eq.setup(u, temp - 1.0, r);
-    const double hdT = half_delta * temp;
-    using S = typename P::S;
-    const size_t plane = (size_t)stride * sizeof(S);
-    static_for<0, Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
+    double rho, temp, half_delta;
+
+    __device__ __forceinline__ void load(const InitFields& f, int64_t cell) {
+        rho = f.rho[cell];
+        temp = f.T[cell];
+        double u[3] = {0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < D; ++k) u[k] = f.u[k * f.N + cell];
+        eq.setup(u, temp - 1.0, f.r);
+        half_delta = f.half_delta;
+    }
+    // g_i and h_i as stored, rounded once, from double, to the storage type
+    // (via float for half)
+    template <class P, int i>
+    __device__ __forceinline__ void values(const WGroups& wg, typename P::S& g,
+                                           typename P::S& h) const {
+        constexpr VelSet<D> V = kVelSet<D>;
         constexpr Vel v = V.v[i];
+        using S = typename P::S;
+        using Mid = std::conditional_t<sizeof(S) < 4, float, S>;
         double A0, A1, A2;  // A0 is A0 - 1 (deviation form)
         eq.template coef<V.qn[v.group]>(A0, A1, A2);
         const double c = eq.template dot<v.x, v.y, v.z>();
         const double pm1 = A0 + c * (A1 + c * (A2 + c * (1.0 / 6.0 + c * (1.0 / 24.0))));
         const double w = wg.w[v.group];
         const double Fdev = w * (rho * pm1 + (rho - 1.0));  // F_i - w_i
+        const double hdT = half_delta * temp;
         double gv, hv;
         if constexpr (P::kDev) {
             gv = Fdev;
@@ -270,17 +282,95 @@ __global__ __launch_bounds__(256) void k_init(char* dst, const double* __restric
             gv = Fdev + w;
             hv = hdT * (Fdev + w);
         }
-        char* base = dst + (size_t)(2 * i) * plane;
         if constexpr (P::kScaled) {  // stored divided by w (see F16Dev)
-            gv /= w;
-            hv /= w;
+            gv = quotient(gv, w, wg.inv_w[v.group]);
+            hv = quotient(hv, w, wg.inv_w[v.group]);
         }
-        // rounded once, from double, to the storage type (via float for half)
-        using Mid = std::conditional_t<sizeof(S) < 4, float, S>;
-        char* at = base + (size_t)cell * cell_bytes(sizeof(S));
-        *reinterpret_cast<S*>(at) = S(Mid(gv));
-        *reinterpret_cast<S*>(at + h_offset(sizeof(S), (uint32_t)plane)) = S(Mid(hv));
+        g = S(Mid(gv));
+        h = S(Mid(hv));
+    }
+};
+
+// S_0 alone (finite differences: no half storage).
+template <int D, class P>
+__global__ __launch_bounds__(256) void k_init(char* dst, const InitFields f, const WGroups wg) {
+    using S = typename P::S;
+    const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
+    if (cell >= f.N) return;
+    InitCell<D> ic;
+    ic.load(f, cell);
+    const size_t plane = (size_t)f.P * sizeof(S);
+    static_for<0, VelSet<D>::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        S g, h;
+        ic.template values<P, i>(wg, g, h);
+        char* at = dst + (size_t)(2 * i) * plane + (size_t)cell * sizeof(S);
+        *reinterpret_cast<S*>(at) = g;
+        *reinterpret_cast<S*>(at + plane) = h;
     });
+}
+
+// S_0 and, from the values as stored, P_0 = Collide(S_0), in the register
+// layouts of the step.  What bounds it is the two sides written: D3Q107 FP32
+// 256^3 5.9 ms (S_0 alone, then a collision that read it again: 2.9 + 5.4), D2Q37
+// FP64 4096^2 3.8 (1.95 + 3.75); in half storage the double arithmetic, FP16
+// 191x173x187 2.3 ms (2.0 + 1.0).
+template <int D, class P, bool SPLIT, int WAVES, bool NT>
+__global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
+void k_init_collide(char* s0, char* p0, const InitFields f, const WGroups wg, const Physics ph) {
+    using T = typename P::T;
+    using S = typename P::S;
+    constexpr int Q = VelSet<D>::Q;
+    constexpr VelSet<D> V = kVelSet<D>;
+    constexpr int L = SPLIT ? 32 : 64;
+    const int lane = (int)threadIdx.x & 63;
+    const int role = SPLIT ? lane >> 5 : 0;
+    const int first = ((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6)) * L;
+    if (first >= (int)f.N) return;
+    // lanes past the last cell repeat it (see k_step)
+    const int cell = min(first + (SPLIT ? (lane & 31) : lane), (int)f.N - 1);
+    const uint32_t plane = (uint32_t)f.P * (uint32_t)sizeof(S);
+    const uint32_t ho = h_offset(sizeof(S), plane);
+    const uint32_t own = (uint32_t)cell * cell_bytes(sizeof(S)) + (role ? ho : 0u);
+    InitCell<D> ic;
+    ic.load(f, cell);
+    if constexpr (SPLIT) {
+        T p[Q];
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            S g, h;
+            ic.template values<P, i>(wg, g, h);
+            const S x = role ? h : g;
+            store_at(s0 + (size_t)(2 * i) * plane, own, x);
+            p[i] = from_store<P>(x, ph, V.v[i].group);
+        });
+        collide_split<D, P>(p, role, ph);
+        store_split<D, P, NT>(p0, plane, own, p, ph);
+    } else if constexpr (P::kScaled) {
+        uint32_t w[Q];
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            S g, h;
+            ic.template values<P, i>(wg, g, h);
+            w[i] = (uint32_t)__builtin_bit_cast(uint16_t, g) |
+                   (uint32_t)__builtin_bit_cast(uint16_t, h) << 16;
+            store_at(s0 + (size_t)(2 * i) * plane, own, w[i]);
+        });
+        collide_words<D, P, NT>(w, p0, plane, own, ph);
+    } else {
+        T g[Q], h[Q];
+        static_for<0, Q>([&](auto I) {
+            constexpr int i = decltype(I)::value;
+            ic.template values<P, i>(wg, g[i], h[i]);
+            // the collision takes the values as stored, not the products
+            // they were rounded from
+            asm("" : "+v"(g[i]), "+v"(h[i]));
+            store_at(s0 + (size_t)(2 * i) * plane, own, g[i]);
+            store_at(s0 + (size_t)(2 * i) * plane + ho, own, h[i]);
+        });
+        collide_lane<D, P>(g, h, ph);
+        store_lane<D, P, NT>(p0, plane, own, g, h, ph);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -347,16 +437,19 @@ __global__ __launch_bounds__(kReadBlock) void k_readout(const ReadArgs a) {
     constexpr VelSet<D> V = kVelSet<D>;
     constexpr int Q = VelSet<D>::Q;
     constexpr int NT = D + 2;
-    const int64_t cell = (int64_t)blockIdx.x * kReadBlock + threadIdx.x;
+    // tiles of kReadBlock cells, dealt to the XCDs in runs like the step's
+    // (wave_cells): the cache lines that shifted pulls share are fetched once
+    const int b = (int)blockIdx.x, j = b >> 3;
+    const int tile = ((j / a.run) * 8 + (b & 7)) * a.run + j % a.run;
+    if (tile >= a.blocks) return;  // the whole workgroup
+    const int64_t cell = (int64_t)tile * kReadBlock + threadIdx.x;
     double tot[NT];
 #pragma unroll
     for (int k = 0; k < NT; ++k) tot[k] = 0.0;
     if (cell < a.N) {
-        int x, y, z;
-        coords((int)cell, a.nx, a.nxy, x, y, z);
-        PullTable<D> pt;
-        pt.fill(x, y, z, a.nx, a.ny, a.nz, a.nxy, a.open_end, a.stream != 0);
         using S = typename P::S;
+        CellOffsets<D, S> o;
+        o.fill((int)cell, a.nx, a.ny, a.nz, a.nxy, a.pull, 0u);
         constexpr bool DEV = P::kDev;
         const uint32_t plane = (uint32_t)a.P * (uint32_t)sizeof(S);
         const char* src = static_cast<const char*>(a.src);
@@ -364,8 +457,7 @@ __global__ __launch_bounds__(kReadBlock) void k_readout(const ReadArgs a) {
         static_for<0, Q>([&](auto I) {
             constexpr int i = decltype(I)::value;
             constexpr Vel v = V.v[i];
-            const uint32_t off =
-                (uint32_t)pt.template src<v.x, v.y, v.z>() * cell_bytes(sizeof(S));
+            const uint32_t off = o.template src<v.x, v.y, v.z>();
             const char* base = src + (size_t)(2 * i) * plane;
             const double scale = P::kScaled ? a.w[v.group] : 1.0;
             const double gv = (double)load_at<S>(base, off) * scale;
@@ -416,7 +508,7 @@ __global__ __launch_bounds__(kReadBlock) void k_readout(const ReadArgs a) {
     if (threadIdx.x < NT) {
         double v = 0.0;
         for (int w = 0; w < kReadBlock / 64; ++w) v += wsum[w][threadIdx.x];
-        a.partials[(int64_t)blockIdx.x * NT + threadIdx.x] = v;
+        a.partials[(int64_t)tile * NT + threadIdx.x] = v;
     }
 }
 
@@ -445,10 +537,53 @@ __global__ __launch_bounds__(256) void k_final_reduce(const double* __restrict__
     if (threadIdx.x < NT) out[threadIdx.x] = sm[0][threadIdx.x];
 }
 
+// Occupancy hint for the split D3Q107 float kernels: asking for at least
+// two waves per SIMD gave 4% more bandwidth than the compiler's own
+// choice (three waves at 162 VGPRs).  In double, two waves (256 VGPRs,
+// 30 values spilled to scratch, against one wave at 256 + 28 AGPRs) ran
+// 2.4% faster in isolated timings but not in the benchmark, and the
+// spills added 13% to the HBM bytes; it keeps one.  The other kernels
+// run best as compiled.
+template <int D, class P>
+constexpr int kSplitWaves = (D == 3 && sizeof(typename P::T) == 4) ? 2 : 1;
+
+// Stores of a step (streamed / cached, us): D2Q37 FP32 512^2 (155 MB) 33.0 /
+// 25.1, 700^2 (290 MB) 57.0 / 53.0, FP16 1024^2 (310 MB) 70.6 / 66.9, D3Q107
+// FP32 45x40x40 (123 MB) 30.8 / 25.3; beyond, D3Q107 FP32 64^3 (449 MB)
+// 87.0 / 88.8, 256^3 5149 / 5715; below, FP32 32^3 (56 MB) 13.4 / 14.3, D2Q37
+// 256^2 (39 MB) 11.5 / 11.9.
+bool streamed(int dim, size_t elem, int64_t P) {
+    const int64_t state = state_bytes(dim, elem, P);
+    return state <= (int64_t(64) << 20) || state > (int64_t(304) << 20);
+}
+
+WGroups groups_of(const double* w_group) {
+    WGroups wg;
+    for (int k = 0; k < 10; ++k) {
+        wg.w[k] = w_group[k];
+        wg.inv_w[k] = 1.0 / w_group[k];
+    }
+    return wg;
+}
+
+template <int D, class P>
+hipError_t init_collide_impl(bool split, void* s0, void* p0, const InitFields& f,
+                             const Physics& ph, const double* w_group, hipStream_t s) {
+    const int tile = split ? 128 : 256;
+    const bool nt = streamed(D, sizeof(typename P::S), f.P);
+    auto* kernel = split ? (nt ? &k_init_collide<D, P, true, kSplitWaves<D, P>, true>
+                               : &k_init_collide<D, P, true, kSplitWaves<D, P>, false>)
+                         : (nt ? &k_init_collide<D, P, false, 1, true>
+                               : &k_init_collide<D, P, false, 1, false>);
+    return launch_kernel(kernel, dim3((unsigned)((f.N + tile - 1) / tile)), dim3(256), s,
+                         static_cast<char*>(s0), static_cast<char*>(p0), f, groups_of(w_group),
+                         ph);
+}
+
 template <int D, class P>
 hipError_t step_impl(bool split, const StepArgs& a0, hipStream_t s) {
     StepArgs a = a0;
-    a.pull = pull_grid(a.nx, a.ny, a.nz, a.open_end, a.stream != 0);
+    a.pull = pull_grid(a.nx, a.ny, a.nz, a.open_end);
     const int L = split ? 32 : 64;  // cells per wave
     // Up to one wave for each SIMD of the chip: workgroups of one wave, which
     // spread over all CUs (us a step, four waves / one: D3Q107 FP64 on 23x9x16,
@@ -457,23 +592,9 @@ hipError_t step_impl(bool split, const StepArgs& a0, hipStream_t s) {
     int grid;
     step_tiles(a.N, a.nx, a.waves * L, &a.run, &grid);
     const dim3 block(64 * a.waves);
-    // Occupancy hint for the split D3Q107 float kernels: asking for at least
-    // two waves per SIMD gave 4% more bandwidth than the compiler's own
-    // choice (three waves at 162 VGPRs).  In double, two waves (256 VGPRs,
-    // 30 values spilled to scratch, against one wave at 256 + 28 AGPRs) ran
-    // 2.4% faster in isolated timings but not in the benchmark, and the
-    // spills added 13% to the HBM bytes; it keeps one.  The other kernels
-    // run best as compiled.
-    constexpr int kSplitWaves = (D == 3 && sizeof(typename P::T) == 4) ? 2 : 1;
-    // Stores (streamed / cached, us a step): D2Q37 FP32 512^2 (155 MB) 33.0 /
-    // 25.1, 700^2 (290 MB) 57.0 / 53.0, FP16 1024^2 (310 MB) 70.6 / 66.9, D3Q107
-    // FP32 45x40x40 (123 MB) 30.8 / 25.3; beyond, D3Q107 FP32 64^3 (449 MB)
-    // 87.0 / 88.8, 256^3 5149 / 5715; below, FP32 32^3 (56 MB) 13.4 / 14.3, D2Q37
-    // 256^2 (39 MB) 11.5 / 11.9.
-    const int64_t state = state_bytes(D, sizeof(typename P::S), a.P);
-    const bool nt = state <= (int64_t(64) << 20) || state > (int64_t(304) << 20);
-    auto* kernel = split ? (nt ? &k_step_split<D, P, kSplitWaves, true>
-                               : &k_step_split<D, P, kSplitWaves, false>)
+    const bool nt = streamed(D, sizeof(typename P::S), a.P);
+    auto* kernel = split ? (nt ? &k_step_split<D, P, kSplitWaves<D, P>, true>
+                               : &k_step_split<D, P, kSplitWaves<D, P>, false>)
                          : (nt ? &k_step<D, P, 1, true> : &k_step<D, P, 1, false>);
     return launch_kernel(kernel, dim3(grid), block, s, a);
 }
@@ -500,24 +621,31 @@ hipError_t with_policy(int precision, F&& f) {
     return f(F32Dev{});
 }
 
-hipError_t launch_init(int dim, int precision, void* dst, const double* rho,
-                       const double* u, const double* T, int64_t N, int64_t stride,
-                       double half_delta, double r, const double* w_group, hipStream_t s) {
-    WGroups wg;
-    for (int k = 0; k < 10; ++k) wg.w[k] = w_group[k];
-    const int grid = (int)((N + 255) / 256);
+hipError_t launch_init(int dim, int precision, void* dst, const InitFields& f,
+                       const double* w_group, hipStream_t s) {
+    // no half storage in the finite-difference form (lbm_create_fd refuses it)
+    if (precision == LBM_FP16_SCALED) return hipErrorInvalidValue;
+    const WGroups wg = groups_of(w_group);
+    const int grid = (int)((f.N + 255) / 256);
     char* d = static_cast<char*>(dst);
+    auto* kernel = precision == LBM_FP64 ? (dim == 2 ? &k_init<2, F64> : &k_init<3, F64>)
+                                         : (dim == 2 ? &k_init<2, F32Dev> : &k_init<3, F32Dev>);
+    return launch_kernel(kernel, dim3(grid), dim3(256), s, d, f, wg);
+}
+
+hipError_t launch_init_collide(int dim, int precision, bool split, void* s0, void* p0,
+                               const InitFields& f, const Physics& ph, const double* w_group,
+                               hipStream_t s) {
     return with_policy(precision, [&](auto pol) {
         using P = decltype(pol);
-        if (dim == 2)
-            return launch_kernel(&k_init<2, P>, dim3(grid), dim3(256), s, d, rho, u, T, N, stride, half_delta, r, wg);
-        return launch_kernel(&k_init<3, P>, dim3(grid), dim3(256), s, d, rho, u, T, N, stride, half_delta, r, wg);
+        return dim == 2 ? init_collide_impl<2, P>(split, s0, p0, f, ph, w_group, s)
+                        : init_collide_impl<3, P>(split, s0, p0, f, ph, w_group, s);
     });
 }
 
 hipError_t launch_step_lds(int precision, const StepArgs& a0, hipStream_t s) {
     StepArgs a = a0;
-    if (a.nx % 128 != 0 || !a.stream) return hipErrorInvalidValue;
+    if (a.nx % 128 != 0) return hipErrorInvalidValue;
     a.rows = a.ny * a.nz;
     a.tiles_per_row = a.nx / 128;
     const int grid = 8 * a.tiles_per_row * ((a.rows + 7) / 8);
@@ -552,11 +680,19 @@ hipError_t launch_fd_step(int dim, int precision, bool split, const StepArgs& a,
     return dim == 2 ? fd_step_impl<2, F32Dev>(split, a, s) : fd_step_impl<3, F32Dev>(split, a, s);
 }
 
-hipError_t launch_readout(int dim, int precision, const ReadArgs& a, int blocks, hipStream_t s) {
+hipError_t launch_readout(int dim, int precision, const ReadArgs& a0, int blocks, hipStream_t s) {
+    ReadArgs a = a0;
+    a.pull = pull_grid(a.nx, a.ny, a.nz, a.open_end);
+    if (!a.stream)
+        for (PullAxis& axis : a.pull.axis)
+            for (int32_t& shift : axis.shift) shift = 0;
+    a.blocks = blocks;
+    int grid;
+    step_tiles(a.N, a.nx, kReadBlock, &a.run, &grid);
     return with_policy(precision, [&](auto pol) {
         using P = decltype(pol);
-        if (dim == 2) return launch_kernel(&k_readout<2, P>, dim3(blocks), dim3(kReadBlock), s, a);
-        return launch_kernel(&k_readout<3, P>, dim3(blocks), dim3(kReadBlock), s, a);
+        if (dim == 2) return launch_kernel(&k_readout<2, P>, dim3(grid), dim3(kReadBlock), s, a);
+        return launch_kernel(&k_readout<3, P>, dim3(grid), dim3(kReadBlock), s, a);
     });
 }
 

@@ -25,9 +25,18 @@ struct LatticeTables {
 };
 const LatticeTables& lattice_tables(int dim);
 
-// Group weights by value (kernel argument).
+// Group weights and their reciprocals by value (kernel argument).
 struct WGroups {
-    double w[10];
+    double w[10], inv_w[10];
+};
+
+// Initial fields on the device, and what the equilibrium takes beside them.
+struct InitFields {
+    const double* rho;  // [N]
+    const double* u;    // [D][N]
+    const double* T;    // [N]
+    int64_t N, P;       // cells; plane stride in cells
+    double half_delta, r;
 };
 
 // Physical parameters of one solve as the collision uses them.
@@ -59,8 +68,8 @@ inline Divisor divisor_of(int64_t d) {
 }
 
 // Where a pull reads along one axis of n cells: e = 1, 2, 3 cells away, taken
-// modulo n on a periodic axis (and 0 without streaming), one turn of n (none
-// at open ends) bringing it back.
+// modulo n on a periodic axis, one turn of n (none at open ends) bringing it
+// back.
 struct PullAxis {
     int32_t turn;
     int32_t shift[3];
@@ -69,14 +78,14 @@ struct PullGrid {
     PullAxis axis[3];
     Divisor by_nx, by_nxy;
 };
-inline PullGrid pull_grid(int64_t nx, int64_t ny, int64_t nz, uint32_t open_end, bool stream) {
+inline PullGrid pull_grid(int64_t nx, int64_t ny, int64_t nz, uint32_t open_end) {
     PullGrid g;
     const int64_t n[3] = {nx, ny, nz};
     for (int k = 0; k < 3; ++k) {
         const bool open = open_end >> k & 1u;
         g.axis[k].turn = open ? 0 : (int32_t)n[k];
         for (int e = 1; e <= 3; ++e)
-            g.axis[k].shift[e - 1] = !stream ? 0 : (open ? e : (int32_t)(e % n[k]));
+            g.axis[k].shift[e - 1] = open ? e : (int32_t)(e % n[k]);
     }
     g.by_nx = divisor_of(nx);
     g.by_nxy = divisor_of(nx * ny);
@@ -93,7 +102,6 @@ struct StepArgs {
     int32_t nx, ny, nz;
     int32_t nxy;          // nx * ny
     uint32_t open_end;    // bit k: axis k is zero-gradient, else periodic
-    int32_t stream;       // 1: pull-stream then collide; 0: collide in place
     PullGrid pull;        // lattice step
     int32_t run;          // consecutive tiles an XCD serves (step_tiles)
     int32_t waves;        // waves per workgroup (tile)
@@ -154,6 +162,8 @@ struct ReadArgs {
     int32_t nx, ny, nz, nxy;
     uint32_t open_end;
     int32_t stream;           // 1: the source holds P_{n-1}; pull to get S_n
+    PullGrid pull;            // set by launch_readout, as
+    int32_t run, blocks;      // are the runs of tiles and their number
     double r;
     double rest_energy;       // (D + delta) / 2, added back in deviation storage
     double inv_dof;           // 1 / (D + delta): T = (2E - |u|^2) / (D + delta)
@@ -182,10 +192,12 @@ inline hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block,
 // Kernel launchers (kernels.hip).  `split` selects the layout in which one
 // lane holds the g populations of a cell and its partner lane (lane ^ 32)
 // the h populations.
-hipError_t launch_init(int dim, int precision, void* dst, const double* rho,
-                       const double* u, const double* T, int64_t N, int64_t stride,
-                       double half_delta, double r, const double* w_group,
-                       hipStream_t s);
+hipError_t launch_init(int dim, int precision, void* dst, const InitFields& f,
+                       const double* w_group, hipStream_t s);
+// S_0 into one side and P_0 = Collide(S_0) into the other.
+hipError_t launch_init_collide(int dim, int precision, bool split, void* s0, void* p0,
+                               const InitFields& f, const Physics& ph, const double* w_group,
+                               hipStream_t s);
 // D3Q107 lattice step with the pulled rows staged in LDS (nx a multiple of
 // 128, streaming steps only; hipErrorInvalidValue otherwise).
 hipError_t launch_step_lds(int precision, const StepArgs& a, hipStream_t s);

@@ -566,7 +566,7 @@ static int pool_admit(lbm_pool_handle p, const lbm_request* r, const double* rho
     e.nz = (int32_t)r->nz;
     e.nxy = (int32_t)(r->nx * r->ny);
     e.open_end = (r->bc & 3u) | (((r->bc >> 2) & 3u) << 1) | (((r->bc >> 4) & 3u) << 2);
-    e.pull = lbm::pull_grid(e.nx, e.ny, e.nz, e.open_end, true);
+    e.pull = lbm::pull_grid(e.nx, e.ny, e.nz, e.open_end);
     lbm::step_tiles(sl.N, r->nx, lbm::default_split(r->dim, p->precision) ? 128 : 256, &e.run,
                     &e.tiles);
     e.dim = r->dim;
@@ -618,25 +618,10 @@ static int pool_admit(lbm_pool_handle p, const lbm_request* r, const double* rho
     }
     char* side0 = p->arena + off;
     char* side1 = side0 + bytes / 2;
-    hipError_t e2 = lbm::launch_init(r->dim, p->precision, side1, drho, du, dT, sl.N, sl.P,
-                                     0.5 * delta, ph.r, ph.w, p->stream);
-    if (e2 == hipSuccess) {
-        lbm::StepArgs a;
-        std::memset(&a, 0, sizeof(a));
-        a.src = side1;
-        a.dst = side0;
-        a.N = sl.N;
-        a.P = sl.P;
-        a.nx = e.nx;
-        a.ny = e.ny;
-        a.nz = e.nz;
-        a.nxy = e.nxy;
-        a.open_end = e.open_end;
-        a.stream = 0;
-        a.ph = ph;
-        e2 = lbm::launch_step(r->dim, p->precision, lbm::default_split(r->dim, p->precision), a,
-                              p->stream);
-    }
+    const lbm::InitFields f{drho, du, dT, sl.N, sl.P, 0.5 * delta, ph.r};
+    hipError_t e2 = lbm::launch_init_collide(r->dim, p->precision,
+                                             lbm::default_split(r->dim, p->precision), side1,
+                                             side0, f, ph, ph.w, p->stream);
     if (e2 == hipSuccess) {
         p->h_steps[slot] = 0;
         e2 = hipMemcpyAsync(p->d_steps + slot, p->h_steps + slot, sizeof(int64_t),

@@ -746,8 +746,7 @@ __device__ __forceinline__ void load_lane(const char* src, uint32_t plane,
 }
 
 template <int D, class P, bool NT>
-__device__ __forceinline__ void store_lane(char* dst, uint32_t plane,
-                                           const CellOffsets<D, typename P::S>& o,
+__device__ __forceinline__ void store_lane(char* dst, uint32_t plane, uint32_t own,
                                            const typename P::T* g, const typename P::T* h,
                                            const Physics& ph) {
     constexpr VelSet<D> V = kVelSet<D>;
@@ -756,8 +755,8 @@ __device__ __forceinline__ void store_lane(char* dst, uint32_t plane,
         constexpr int i = decltype(I)::value;
         constexpr int grp = V.v[i].group;
         char* base = dst + (size_t)(2 * i) * plane;
-        store_as<NT>(base, o.own, to_store<P>(g[i], ph, grp));
-        store_as<NT>(base + ho, o.own, to_store<P>(h[i], ph, grp));
+        store_as<NT>(base, own, to_store<P>(g[i], ph, grp));
+        store_as<NT>(base + ho, own, to_store<P>(h[i], ph, grp));
     });
 }
 
@@ -871,6 +870,17 @@ struct PairAcc {
     }
 };
 
+// Collide a cell's words and store them.
+template <int D, class P, bool NT>
+__device__ __forceinline__ void collide_words(uint32_t* w, char* dst, uint32_t plane, uint32_t own,
+                                              const Physics& ph) {
+    collide_lane_acc<D, P, false, true>(PairAcc<D>{w, ph}, ph);
+    static_for<0, VelSet<D>::Q>([&](auto I) {
+        constexpr int i = decltype(I)::value;
+        store_as<NT>(dst + (size_t)(2 * i) * plane, own, w[i]);
+    });
+}
+
 // Pull, collide and store one cell in the lane layout: F64 and F32Dev as
 // g[] and h[] arrays, half storage as g/h words.
 template <int D, class P, bool NT>
@@ -888,16 +898,12 @@ __device__ __forceinline__ void step_lane_cell(const char* src, char* dst, uint3
             w[i] = load_at<uint32_t>(src + (size_t)(2 * i) * plane,
                                      o.template src<v.x, v.y, v.z>());
         });
-        collide_lane_acc<D, P, false, true>(PairAcc<D>{w, ph}, ph);
-        static_for<0, Q>([&](auto I) {
-            constexpr int i = decltype(I)::value;
-            store_as<NT>(dst + (size_t)(2 * i) * plane, o.own, w[i]);
-        });
+        collide_words<D, P, NT>(w, dst, plane, o.own, ph);
     } else {
         T g[Q], h[Q];
         load_lane<D, P>(src, plane, o, g, h, ph);
         collide_lane<D, P>(g, h, ph);
-        store_lane<D, P, NT>(dst, plane, o, g, h, ph);
+        store_lane<D, P, NT>(dst, plane, o.own, g, h, ph);
     }
 }
 
