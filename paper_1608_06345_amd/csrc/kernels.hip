@@ -244,6 +244,26 @@ __device__ __forceinline__ double quotient(double x, double w, double inv_w) {
     return r == r ? __builtin_fma(r, inv_w, q) : q;
 }
 
+// x rounded once to the storage type.  To half by way of the float rounded to
+// odd (truncated, last bit set if that lost anything): it has more than two
+// bits beyond a half's, so the second rounding is that of x itself.  (The
+// compiler's own conversion, in integers, is three times as long.)
+template <typename S>
+__device__ __forceinline__ S stored(double x) {
+    if constexpr (sizeof(S) >= 4) {
+        return S(x);
+    } else {
+        const float f = (float)x;
+        const double e = (double)f;
+        int b = __builtin_bit_cast(int, f);
+        b -= __builtin_fabs(e) > __builtin_fabs(x) ? 1 : 0;
+        b |= e != x ? 1 : 0;
+        float odd = __builtin_bit_cast(float, b);
+        asm("" : "+v"(odd));
+        return S(odd);
+    }
+}
+
 template <int D>
 struct InitCell {
     Equilibrium<D, double, true> eq;  // deviation form, in double
@@ -258,15 +278,12 @@ struct InitCell {
         eq.setup(u, temp - 1.0, f.r);
         half_delta = f.half_delta;
     }
-    // g_i and h_i as stored, rounded once, from double, to the storage type
-    // (via float for half)
+    // g_i and h_i as stored, rounded once, from double
     template <class P, int i>
     __device__ __forceinline__ void values(const WGroups& wg, typename P::S& g,
                                            typename P::S& h) const {
         constexpr VelSet<D> V = kVelSet<D>;
         constexpr Vel v = V.v[i];
-        using S = typename P::S;
-        using Mid = std::conditional_t<sizeof(S) < 4, float, S>;
         double A0, A1, A2;  // A0 is A0 - 1 (deviation form)
         eq.template coef<V.qn[v.group]>(A0, A1, A2);
         const double c = eq.template dot<v.x, v.y, v.z>();
@@ -286,8 +303,8 @@ struct InitCell {
             gv = quotient(gv, w, wg.inv_w[v.group]);
             hv = quotient(hv, w, wg.inv_w[v.group]);
         }
-        g = S(Mid(gv));
-        h = S(Mid(hv));
+        g = stored<typename P::S>(gv);
+        h = stored<typename P::S>(hv);
     }
 };
 
@@ -313,8 +330,8 @@ __global__ __launch_bounds__(256) void k_init(char* dst, const InitFields f, con
 // S_0 and, from the values as stored, P_0 = Collide(S_0), in the register
 // layouts of the step.  What bounds it is the two sides written: D3Q107 FP32
 // 256^3 5.9 ms (S_0 alone, then a collision that read it again: 2.9 + 5.4), D2Q37
-// FP64 4096^2 3.8 (1.95 + 3.75); in half storage the double arithmetic, FP16
-// 191x173x187 2.3 ms (2.0 + 1.0).
+// FP64 4096^2 3.8 (1.95 + 3.75); in half storage also the double arithmetic, FP16
+// 191x173x187 1.49 ms (2.0 + 1.0; 2.30 with the compiler's conversion to half).
 template <int D, class P, bool SPLIT, int WAVES, bool NT>
 __global__ __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(WAVES, 8)))
 void k_init_collide(char* s0, char* p0, const InitFields f, const WGroups wg, const Physics ph) {

@@ -83,20 +83,9 @@ struct PullTable {
     }
 };
 
-
 // n / d for 0 <= n < 2^31 (see Divisor).
 __device__ __forceinline__ int divide(int n, Divisor d) {
     return (int)(__umulhi((uint32_t)n << 1, d.mul) >> d.shift);
-}
-
-// Cell -> (x, y, z).  Unsigned: a cell index is below 2^31 and the unsigned
-// division is the shorter one.
-__device__ __forceinline__ void coords(int cell, int nx, int nxy, int& x, int& y,
-                                       int& z) {
-    z = (int)((uint32_t)cell / (uint32_t)nxy);
-    const int rem = cell - z * nxy;
-    y = (int)((uint32_t)rem / (uint32_t)nx);
-    x = rem - y * nx;
 }
 
 // The 4th-order equilibrium of one cell, as a polynomial in c = xi . u per
