@@ -256,7 +256,8 @@ typedef struct {
     uint32_t bc;
     double gamma, delta, tau_f, tau_g, r;
     int64_t steps;          /* steps taken since the last init */
-    size_t device_bytes;    /* device memory held by the handle */
+    size_t device_bytes;    /* device memory of the solve (host-array calls hold up to
+                               16 MiB more, as staging) */
     int scheme;             /* 0: lattice streaming, 1: finite differences */
     double dt;              /* finite-difference time step (0 for lattice) */
     int collision;          /* enum lbm_collision */
@@ -281,15 +282,16 @@ int lbm_lattice(int velocity_set, int8_t *e, double *w, double *r);
  * Many independent solves -- D2Q37 and D3Q107 grids of any size, each with
  * its own gamma, tau_f, tau_g, boundary conditions and number of steps --
  * stay resident in one device arena and are advanced together: every step is
- * one launch per velocity set over all resident solves (plus one tiny
- * counter launch), and lbm_pool_run replays K such steps from a captured
+ * one launch per velocity set over all resident solves (and a run ends with
+ * one tiny counter launch), and lbm_pool_run replays K such steps from a captured
  * hipGraph.  Membership lives in device tables, so solves can be admitted and
  * released between replays without re-capturing (continuous batching).  Each
  * solve follows exactly the single-solve scheme and state convention above
  * (lattice streaming, the paper's collision: the finite-difference form and
  * the energy-conserving collision are single-solve options); its arithmetic
  * does not depend on which other solves are resident.
- * All pool memory is owned by the pool.  A pool is not thread-safe.
+ * All pool memory is owned by the pool; beside the arena it holds the fields of
+ * the largest solve set or read with host arrays.  A pool is not thread-safe.
  * ---------------------------------------------------------------------- */
 typedef struct lbm_pool *lbm_pool_handle;
 

@@ -2,6 +2,7 @@
 // Every entry point validates its arguments on the host, checks every HIP
 // call, and returns an lbm_status code; no exception crosses the boundary.
 #include <cmath>
+#include <cstdlib>
 #include <cstring>
 #include <new>
 
@@ -135,6 +136,93 @@ int create_solver(int dim, int velocity_set, double gamma, double tau_f, double 
                   lbm_handle* out);
 
 }  // namespace
+
+hipError_t lbm::HostStage::reserve(size_t need) {
+    if (need <= bytes) return hipSuccess;
+    if (dev) (void)hipFree(dev);
+    dev = nullptr;
+    bytes = 0;
+    const hipError_t e = hipMalloc((void**)&dev, need);
+    if (e == hipSuccess) bytes = need;
+    return e;
+}
+
+void lbm::HostStage::done() {
+    if (bytes <= kKeep) return;
+    (void)hipFree(dev);
+    dev = nullptr;
+    bytes = 0;
+}
+
+void lbm::HostStage::release() {
+    if (dev) (void)hipFree(dev);
+    std::free(host);
+    dev = host = nullptr;
+    bytes = 0;
+}
+
+namespace {
+
+// The host block, or null (not for this size, or none to be had: the copies
+// then go array by array).
+double* host_block(lbm::HostStage& st, size_t need) {
+    if (need > lbm::HostStage::kOneCopy) return nullptr;
+    if (!st.host) st.host = static_cast<double*>(std::malloc(lbm::HostStage::kOneCopy));
+    return st.host;
+}
+
+size_t sum_of(const size_t* sizes, int n) {
+    size_t t = 0;
+    for (int k = 0; k < n; ++k) t += sizes[k];
+    return t;
+}
+
+}  // namespace
+
+hipError_t lbm::HostStage::to_device(const double* const* src, const size_t* sizes, int n,
+                                     hipStream_t s) {
+    const size_t total = sum_of(sizes, n) * sizeof(double);
+    double* one = host_block(*this, total);
+    size_t at = 0;
+    for (int k = 0; k < n; ++k) {
+        const size_t b = sizes[k] * sizeof(double);
+        if (one) {
+            std::memcpy(one + at, src[k], b);
+        } else {
+            const hipError_t e = hipMemcpyAsync(dev + at, src[k], b, hipMemcpyHostToDevice, s);
+            if (e != hipSuccess) return e;
+        }
+        at += sizes[k];
+    }
+    return one ? hipMemcpyAsync(dev, one, total, hipMemcpyHostToDevice, s) : hipSuccess;
+}
+
+hipError_t lbm::HostStage::to_host(double* const* dst, const size_t* sizes, int n,
+                                   hipStream_t s) {
+    const size_t total = sum_of(sizes, n) * sizeof(double);
+    double* one = host_block(*this, total);
+    if (one) {
+        hipError_t e = hipMemcpyAsync(one, dev, total, hipMemcpyDeviceToHost, s);
+        const hipError_t es = hipStreamSynchronize(s);
+        if (e == hipSuccess) e = es;
+        if (e != hipSuccess) return e;
+    }
+    size_t at = 0;
+    for (int k = 0; k < n; ++k) {
+        const size_t b = sizes[k] * sizeof(double);
+        if (one) {
+            std::memcpy(dst[k], one + at, b);
+        } else {
+            const hipError_t e = hipMemcpyAsync(dst[k], dev + at, b, hipMemcpyDeviceToHost, s);
+            if (e != hipSuccess) {
+                (void)hipStreamSynchronize(s);
+                return e;
+            }
+        }
+        at += sizes[k];
+    }
+    return one ? hipSuccess : hipStreamSynchronize(s);
+}
 
 int lbm::solver_readout(lbm_solver* h, double* rho, double* u, double* E, double* T,
                         bool totals) {
@@ -310,6 +398,7 @@ int lbm_destroy(lbm_handle h) {
     if (h->partials) (void)hipFree(h->partials);
     if (h->totals) (void)hipFree(h->totals);
     if (h->fd_record) (void)hipFree(h->fd_record);
+    h->stage.release();
     if (h->own_stream) (void)hipStreamDestroy(h->own_stream);
     delete h;
     return LBM_OK;
@@ -396,17 +485,15 @@ int lbm_init_fields_dev(lbm_handle h, const double* rho, const double* u, const 
 
 int lbm_init_fields(lbm_handle h, const double* rho, const double* u, const double* T) {
     if (!h || !rho || !u || !T) return LBM_EINVAL;
-    const size_t n = (size_t)h->N * sizeof(double);
-    double* d = nullptr;
-    LBM_HIP(hipMalloc((void**)&d, n * (2 + h->dim)));
-    hipError_t e = hipMemcpyAsync(d, rho, n, hipMemcpyHostToDevice, h->stream);
-    if (e == hipSuccess) e = hipMemcpyAsync(d + h->N, T, n, hipMemcpyHostToDevice, h->stream);
-    if (e == hipSuccess)
-        e = hipMemcpyAsync(d + 2 * h->N, u, n * h->dim, hipMemcpyHostToDevice, h->stream);
-    int rc = dev_err(e);
-    if (rc == LBM_OK) rc = lbm_init_fields_dev(h, d, d + 2 * h->N, d + h->N);
+    const size_t n = (size_t)h->N;
+    LBM_HIP(h->stage.reserve(n * (2 + h->dim) * sizeof(double)));
+    double* d = h->stage.dev;
+    const double* src[3] = {rho, T, u};
+    const size_t sizes[3] = {n, n, n * h->dim};
+    int rc = dev_err(h->stage.to_device(src, sizes, 3, h->stream));
+    if (rc == LBM_OK) rc = lbm_init_fields_dev(h, d, d + 2 * n, d + n);
     const hipError_t es = hipStreamSynchronize(h->stream);
-    (void)hipFree(d);
+    h->stage.done();
     if (rc != LBM_OK) return rc;
     return dev_err(es);
 }
@@ -443,21 +530,16 @@ int lbm_moments_dev(lbm_handle h, double* rho, double* u, double* E) {
 int lbm_moments(lbm_handle h, double* rho, double* u, double* E) {
     if (!h || !rho || !u || !E) return LBM_EINVAL;
     if (!h->have_state) return LBM_ESTATE;
-    const size_t n = (size_t)h->N * sizeof(double);
-    double* d = nullptr;
-    LBM_HIP(hipMalloc((void**)&d, n * (2 + h->dim)));
-    int rc = readout(h, d, d + 2 * h->N, d + h->N, nullptr, false);
-    hipError_t e = hipSuccess;
-    if (rc == LBM_OK) e = hipMemcpyAsync(rho, d, n, hipMemcpyDeviceToHost, h->stream);
-    if (rc == LBM_OK && e == hipSuccess)
-        e = hipMemcpyAsync(E, d + h->N, n, hipMemcpyDeviceToHost, h->stream);
-    if (rc == LBM_OK && e == hipSuccess)
-        e = hipMemcpyAsync(u, d + 2 * h->N, n * h->dim, hipMemcpyDeviceToHost, h->stream);
-    const hipError_t es = hipStreamSynchronize(h->stream);
-    (void)hipFree(d);
-    if (rc != LBM_OK) return rc;
-    if (e != hipSuccess) return dev_err(e);
-    return dev_err(es);
+    const size_t n = (size_t)h->N;
+    LBM_HIP(h->stage.reserve(n * (2 + h->dim) * sizeof(double)));
+    double* d = h->stage.dev;
+    double* dst[3] = {rho, E, u};
+    const size_t sizes[3] = {n, n, n * h->dim};
+    int rc = readout(h, d, d + 2 * n, d + n, nullptr, false);
+    if (rc == LBM_OK) rc = dev_err(h->stage.to_host(dst, sizes, 3, h->stream));
+    else (void)hipStreamSynchronize(h->stream);
+    h->stage.done();
+    return rc;
 }
 
 int lbm_temperature_dev(lbm_handle h, double* T) {
@@ -469,17 +551,13 @@ int lbm_temperature_dev(lbm_handle h, double* T) {
 int lbm_temperature(lbm_handle h, double* T) {
     if (!h || !T) return LBM_EINVAL;
     if (!h->have_state) return LBM_ESTATE;
-    const size_t n = (size_t)h->N * sizeof(double);
-    double* d = nullptr;
-    LBM_HIP(hipMalloc((void**)&d, n));
-    int rc = readout(h, nullptr, nullptr, nullptr, d, false);
-    hipError_t e = hipSuccess;
-    if (rc == LBM_OK) e = hipMemcpyAsync(T, d, n, hipMemcpyDeviceToHost, h->stream);
-    const hipError_t es = hipStreamSynchronize(h->stream);
-    (void)hipFree(d);
-    if (rc != LBM_OK) return rc;
-    if (e != hipSuccess) return dev_err(e);
-    return dev_err(es);
+    const size_t n = (size_t)h->N;
+    LBM_HIP(h->stage.reserve(n * sizeof(double)));
+    int rc = readout(h, nullptr, nullptr, nullptr, h->stage.dev, false);
+    if (rc == LBM_OK) rc = dev_err(h->stage.to_host(&T, &n, 1, h->stream));
+    else (void)hipStreamSynchronize(h->stream);
+    h->stage.done();
+    return rc;
 }
 
 int lbm_totals(lbm_handle h, double* mass, double* mom, double* energy) {

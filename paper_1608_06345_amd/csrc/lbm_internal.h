@@ -228,6 +228,31 @@ constexpr int kReadBlock = 256;
 
 struct lbm_solver;
 namespace lbm {
+
+// Staging of the host-array calls of one solve: a device buffer and, for up to
+// kOneCopy bytes, a host block that lets all arrays of a call go as one copy.
+// Made on first use; the device buffer is kept up to kKeep bytes and freed with
+// the call above (an allocation is small beside those copies).  What bounds the
+// small calls is the runtime's time per copy, 6 to 8 us each: moments of D2Q37
+// FP64 200x4 55 -> 30 us; from 256 KiB on the copies' own bytes take over
+// (1000x16: 68 -> 66 us).  A pinned block gains 1 to 4 us more on a call, but
+// costs each solve 0.1 ms to allocate and free.
+struct HostStage {
+    static constexpr size_t kKeep = size_t(16) << 20;
+    static constexpr size_t kOneCopy = size_t(256) << 10;
+    double* dev;
+    size_t bytes;
+    double* host;  // kOneCopy bytes
+
+    hipError_t reserve(size_t need);
+    void done();     // after the call's work has ended
+    void release();
+    // n arrays of sizes[k] values, one after the other in `dev`, to or from
+    // host memory on stream s; from the device: waits for s.
+    hipError_t to_device(const double* const* src, const size_t* sizes, int n, hipStream_t s);
+    hipError_t to_host(double* const* dst, const size_t* sizes, int n, hipStream_t s);
+};
+
 // Readout of a solve's S_n into device outputs (any may be null), with the
 // FP64 totals into the solve's own buffer when `totals` (api.hip).
 int solver_readout(lbm_solver* h, double* rho, double* u, double* E, double* T, bool totals);
@@ -262,5 +287,6 @@ struct lbm_solver {
     bool fd_fused;        // finite differences: one fused kernel (LANE / SPLIT variants)
     void* fd_record;      // finite differences, two passes: per-cell record
     bool fd_record_valid; // the record describes the current state
+    lbm::HostStage stage; // fields of host-array calls
     size_t device_bytes;
 };

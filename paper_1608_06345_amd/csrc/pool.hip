@@ -223,7 +223,7 @@ struct lbm_pool {
     SolveEntry* d_table = nullptr;
     int64_t* d_steps = nullptr;
     char* d_dir[2] = {nullptr, nullptr};  // TileDir + begin[] + slot[] per velocity set
-    double* d_stage = nullptr;            // initial fields of an admission
+    double* d_stage = nullptr;            // initial fields of an admission, readouts to the host
     size_t stage_cells = 0;
     double* d_partials = nullptr;
     size_t partial_blocks = 0;
@@ -361,6 +361,21 @@ int ensure_partials(lbm_pool* p, int64_t N) {
     p->partial_blocks = 0;
     POOL_HIP(hipMalloc((void**)&p->d_partials, blocks * 5 * sizeof(double)));
     p->partial_blocks = blocks;
+    return LBM_OK;
+}
+
+// Staging for `need` values of initial fields or readouts (every call that
+// uses it waits for the stream before it returns).
+int ensure_stage(lbm_pool* p, size_t need) {
+    if (need <= p->stage_cells) return LBM_OK;
+    if (p->d_stage) {
+        POOL_HIP(hipStreamSynchronize(p->stream));
+        POOL_HIP(hipFree(p->d_stage));
+    }
+    p->d_stage = nullptr;
+    p->stage_cells = 0;
+    POOL_HIP(hipMalloc((void**)&p->d_stage, need * sizeof(double)));
+    p->stage_cells = need;
     return LBM_OK;
 }
 
@@ -592,18 +607,8 @@ static int pool_admit(lbm_pool_handle p, const lbm_request* r, const double* rho
     };
     if (!device) {
         const size_t need = (size_t)sl.N * (2 + r->dim);
-        if (need > p->stage_cells) {
-            if (p->d_stage) {
-                hipError_t e2 = hipStreamSynchronize(p->stream);
-                if (e2 == hipSuccess) e2 = hipFree(p->d_stage);
-                if (e2 != hipSuccess) return fail(lbm::err_of(e2));
-            }
-            p->d_stage = nullptr;
-            p->stage_cells = 0;
-            hipError_t e2 = hipMalloc((void**)&p->d_stage, need * sizeof(double));
-            if (e2 != hipSuccess) return fail(lbm::err_of(e2));
-            p->stage_cells = need;
-        }
+        const int rs = ensure_stage(p, need);
+        if (rs != LBM_OK) return fail(rs);
         const size_t nb = (size_t)sl.N * sizeof(double);
         hipError_t e2 = hipMemcpyAsync(p->d_stage, rho, nb, hipMemcpyHostToDevice, p->stream);
         if (e2 == hipSuccess)
@@ -752,8 +757,9 @@ int lbm_pool_moments(lbm_pool_handle p, int slot, double* rho, double* u, double
     if (!rho || !u || !E) return LBM_EINVAL;
     const Slot& sl = p->slots[slot];
     const size_t n = (size_t)sl.N * sizeof(double);
-    double* d = nullptr;
-    POOL_HIP(hipMalloc((void**)&d, n * (2 + sl.dim)));
+    rc = ensure_stage(p, (size_t)sl.N * (2 + sl.dim));
+    if (rc != LBM_OK) return rc;
+    double* d = p->d_stage;
     rc = pool_readout(p, slot, d, d + 2 * sl.N, d + sl.N, nullptr, false);
     hipError_t e = hipSuccess;
     if (rc == LBM_OK) e = hipMemcpyAsync(rho, d, n, hipMemcpyDeviceToHost, p->stream);
@@ -762,7 +768,6 @@ int lbm_pool_moments(lbm_pool_handle p, int slot, double* rho, double* u, double
     if (rc == LBM_OK && e == hipSuccess)
         e = hipMemcpyAsync(u, d + 2 * sl.N, n * sl.dim, hipMemcpyDeviceToHost, p->stream);
     const hipError_t es = hipStreamSynchronize(p->stream);
-    (void)hipFree(d);
     if (rc != LBM_OK) return rc;
     if (e != hipSuccess) return lbm::err_of(e);
     return lbm::err_of(es);
@@ -779,14 +784,14 @@ int lbm_pool_temperature(lbm_pool_handle p, int slot, double* T) {
     int rc = check_slot(p, slot);
     if (rc != LBM_OK) return rc;
     if (!T) return LBM_EINVAL;
-    const size_t n = (size_t)p->slots[slot].N * sizeof(double);
-    double* d = nullptr;
-    POOL_HIP(hipMalloc((void**)&d, n));
-    rc = pool_readout(p, slot, nullptr, nullptr, nullptr, d, false);
+    const size_t N = (size_t)p->slots[slot].N;
+    rc = ensure_stage(p, N);
+    if (rc != LBM_OK) return rc;
+    rc = pool_readout(p, slot, nullptr, nullptr, nullptr, p->d_stage, false);
     hipError_t e = hipSuccess;
-    if (rc == LBM_OK) e = hipMemcpyAsync(T, d, n, hipMemcpyDeviceToHost, p->stream);
+    if (rc == LBM_OK)
+        e = hipMemcpyAsync(T, p->d_stage, N * sizeof(double), hipMemcpyDeviceToHost, p->stream);
     const hipError_t es = hipStreamSynchronize(p->stream);
-    (void)hipFree(d);
     if (rc != LBM_OK) return rc;
     if (e != hipSuccess) return lbm::err_of(e);
     return lbm::err_of(es);
