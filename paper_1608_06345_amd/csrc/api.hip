@@ -463,8 +463,13 @@ int lbm_init_fields_dev(lbm_handle h, const double* rho, const double* u, const 
     if (!h || !rho || !u || !T) return LBM_EINVAL;
     const lbm::InitFields f{rho, u, T, h->N, h->P, 0.5 * h->delta, h->lat->r};
     if (h->scheme) {  // finite differences keep S_n itself
-        LBM_HIP(lbm::launch_init(h->dim, h->precision, h->buf[0], f, h->lat->w_group, h->stream));
+        // the record too, where the steps work from it
+        void* record = h->fd_fused ? nullptr : h->fd_record;
         h->fd_record_valid = false;
+        LBM_HIP(lbm::launch_fd_init(h->dim, h->precision, h->buf[0], record, f,
+                                    step_args(h, nullptr, nullptr).ph, h->lat->w_group,
+                                    h->stream));
+        h->fd_record_valid = record != nullptr;
         h->cur = 0;
         h->initial = true;
         h->have_state = true;

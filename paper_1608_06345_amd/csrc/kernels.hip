@@ -230,103 +230,6 @@ void k_step_split_lds(const StepArgs a) {
 }
 
 // ---------------------------------------------------------------------------
-// Initial state S_0 = equilibrium of (rho, u, T), evaluated in double and
-// stored in the storage precision (deviation from the rest equilibrium in
-// FP32_DEV: g_i - w_i, h_i - (delta/2) w_i).
-//
-// x / w, with 1 / w (rounded once) at hand: the first quotient is within an
-// ulp, its remainder exact, and the corrected one is x / w rounded once
-// (Markstein's division).  A remainder that is not a number leaves the first.
-__device__ __forceinline__ double quotient(double x, double w, double inv_w) {
-#pragma clang fp contract(off)
-    const double q = x * inv_w;
-    const double r = __builtin_fma(-q, w, x);
-    return r == r ? __builtin_fma(r, inv_w, q) : q;
-}
-
-// x rounded once to the storage type.  To half by way of the float rounded to
-// odd (truncated, last bit set if that lost anything): it has more than two
-// bits beyond a half's, so the second rounding is that of x itself.  (The
-// compiler's own conversion, in integers, is three times as long.)
-template <typename S>
-__device__ __forceinline__ S stored(double x) {
-    if constexpr (sizeof(S) >= 4) {
-        return S(x);
-    } else {
-        const float f = (float)x;
-        const double e = (double)f;
-        int b = __builtin_bit_cast(int, f);
-        b -= __builtin_fabs(e) > __builtin_fabs(x) ? 1 : 0;
-        b |= e != x ? 1 : 0;
-        float odd = __builtin_bit_cast(float, b);
-        asm("" : "+v"(odd));
-        return S(odd);
-    }
-}
-
-template <int D>
-struct InitCell {
-    Equilibrium<D, double, true> eq;  // deviation form, in double
-    double rho, temp, half_delta;
-
-    __device__ __forceinline__ void load(const InitFields& f, int64_t cell) {
-        rho = f.rho[cell];
-        temp = f.T[cell];
-        double u[3] = {0, 0, 0};
-#pragma unroll
-        for (int k = 0; k < D; ++k) u[k] = f.u[k * f.N + cell];
-        eq.setup(u, temp - 1.0, f.r);
-        half_delta = f.half_delta;
-    }
-    // g_i and h_i as stored, rounded once, from double
-    template <class P, int i>
-    __device__ __forceinline__ void values(const WGroups& wg, typename P::S& g,
-                                           typename P::S& h) const {
-        constexpr VelSet<D> V = kVelSet<D>;
-        constexpr Vel v = V.v[i];
-        double A0, A1, A2;  // A0 is A0 - 1 (deviation form)
-        eq.template coef<V.qn[v.group]>(A0, A1, A2);
-        const double c = eq.template dot<v.x, v.y, v.z>();
-        const double pm1 = A0 + c * (A1 + c * (A2 + c * (1.0 / 6.0 + c * (1.0 / 24.0))));
-        const double w = wg.w[v.group];
-        const double Fdev = w * (rho * pm1 + (rho - 1.0));  // F_i - w_i
-        const double hdT = half_delta * temp;
-        double gv, hv;
-        if constexpr (P::kDev) {
-            gv = Fdev;
-            hv = hdT * Fdev + half_delta * w * (temp - 1.0);  // H_i - (delta/2) w_i
-        } else {
-            gv = Fdev + w;
-            hv = hdT * (Fdev + w);
-        }
-        if constexpr (P::kScaled) {  // stored divided by w (see F16Dev)
-            gv = quotient(gv, w, wg.inv_w[v.group]);
-            hv = quotient(hv, w, wg.inv_w[v.group]);
-        }
-        g = stored<typename P::S>(gv);
-        h = stored<typename P::S>(hv);
-    }
-};
-
-// S_0 alone (finite differences: no half storage).
-template <int D, class P>
-__global__ __launch_bounds__(256) void k_init(char* dst, const InitFields f, const WGroups wg) {
-    using S = typename P::S;
-    const int64_t cell = (int64_t)blockIdx.x * 256 + threadIdx.x;
-    if (cell >= f.N) return;
-    InitCell<D> ic;
-    ic.load(f, cell);
-    const size_t plane = (size_t)f.P * sizeof(S);
-    static_for<0, VelSet<D>::Q>([&](auto I) {
-        constexpr int i = decltype(I)::value;
-        S g, h;
-        ic.template values<P, i>(wg, g, h);
-        char* at = dst + (size_t)(2 * i) * plane + (size_t)cell * sizeof(S);
-        *reinterpret_cast<S*>(at) = g;
-        *reinterpret_cast<S*>(at + plane) = h;
-    });
-}
-
 // S_0 and, from the values as stored, P_0 = Collide(S_0), in the register
 // layouts of the step.  What bounds it is the two sides written: D3Q107 FP32
 // 256^3 5.9 ms (S_0 alone, then a collision that read it again: 2.9 + 5.4), D2Q37
@@ -574,15 +477,6 @@ bool streamed(int dim, size_t elem, int64_t P) {
     return state <= (int64_t(64) << 20) || state > (int64_t(304) << 20);
 }
 
-WGroups groups_of(const double* w_group) {
-    WGroups wg;
-    for (int k = 0; k < 10; ++k) {
-        wg.w[k] = w_group[k];
-        wg.inv_w[k] = 1.0 / w_group[k];
-    }
-    return wg;
-}
-
 template <int D, class P>
 hipError_t init_collide_impl(bool split, void* s0, void* p0, const InitFields& f,
                              const Physics& ph, const double* w_group, hipStream_t s) {
@@ -636,18 +530,6 @@ hipError_t with_policy(int precision, F&& f) {
     if (precision == LBM_FP64) return f(F64{});
     if (precision == LBM_FP16_SCALED) return f(F16Dev{});
     return f(F32Dev{});
-}
-
-hipError_t launch_init(int dim, int precision, void* dst, const InitFields& f,
-                       const double* w_group, hipStream_t s) {
-    // no half storage in the finite-difference form (lbm_create_fd refuses it)
-    if (precision == LBM_FP16_SCALED) return hipErrorInvalidValue;
-    const WGroups wg = groups_of(w_group);
-    const int grid = (int)((f.N + 255) / 256);
-    char* d = static_cast<char*>(dst);
-    auto* kernel = precision == LBM_FP64 ? (dim == 2 ? &k_init<2, F64> : &k_init<3, F64>)
-                                         : (dim == 2 ? &k_init<2, F32Dev> : &k_init<3, F32Dev>);
-    return launch_kernel(kernel, dim3(grid), dim3(256), s, d, f, wg);
 }
 
 hipError_t launch_init_collide(int dim, int precision, bool split, void* s0, void* p0,

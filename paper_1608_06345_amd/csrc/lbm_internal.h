@@ -29,6 +29,14 @@ const LatticeTables& lattice_tables(int dim);
 struct WGroups {
     double w[10], inv_w[10];
 };
+inline WGroups groups_of(const double* w_group) {
+    WGroups wg;
+    for (int k = 0; k < 10; ++k) {
+        wg.w[k] = w_group[k];
+        wg.inv_w[k] = 1.0 / w_group[k];
+    }
+    return wg;
+}
 
 // Initial fields on the device, and what the equilibrium takes beside them.
 struct InitFields {
@@ -192,8 +200,6 @@ inline hipError_t launch_kernel(void (*kernel)(KArgs...), dim3 grid, dim3 block,
 // Kernel launchers (kernels.hip).  `split` selects the layout in which one
 // lane holds the g populations of a cell and its partner lane (lane ^ 32)
 // the h populations.
-hipError_t launch_init(int dim, int precision, void* dst, const InitFields& f,
-                       const double* w_group, hipStream_t s);
 // S_0 into one side and P_0 = Collide(S_0) into the other.
 hipError_t launch_init_collide(int dim, int precision, bool split, void* s0, void* p0,
                                const InitFields& f, const Physics& ph, const double* w_group,
@@ -212,6 +218,9 @@ hipError_t launch_fd_step(int dim, int precision, bool split, const StepArgs& a,
 // the next step's record behind (record_valid: skip the moments pass).
 // FP64 and FP32 deviation storage.
 size_t fd_record_bytes(int dim, int precision, int64_t P);
+// S_0 of the finite-difference form and, unless `record` is null, its record.
+hipError_t launch_fd_init(int dim, int precision, void* dst, void* record, const InitFields& f,
+                          const Physics& ph, const double* w_group, hipStream_t s);
 hipError_t launch_fd_two_pass(int dim, int precision, const StepArgs& a, void* record,
                               bool record_valid, hipStream_t s);
 // Launch shape of a lattice step over N cells in rows of nx, with workgroups

@@ -976,5 +976,83 @@ __device__ __forceinline__ void convect_store_lane(const char* src, char* dst, u
     });
 }
 
+// Initial state S_0 = equilibrium of (rho, u, T), evaluated in double and
+// stored in the storage precision (deviation from the rest equilibrium in
+// FP32_DEV: g_i - w_i, h_i - (delta/2) w_i).
+//
+// x / w, with 1 / w (rounded once) at hand: the first quotient is within an
+// ulp, its remainder exact, and the corrected one is x / w rounded once
+// (Markstein's division).  A remainder that is not a number leaves the first.
+__device__ __forceinline__ double quotient(double x, double w, double inv_w) {
+#pragma clang fp contract(off)
+    const double q = x * inv_w;
+    const double r = __builtin_fma(-q, w, x);
+    return r == r ? __builtin_fma(r, inv_w, q) : q;
+}
+
+// x rounded once to the storage type.  To half by way of the float rounded to
+// odd (truncated, last bit set if that lost anything): it has more than two
+// bits beyond a half's, so the second rounding is that of x itself.  (The
+// compiler's own conversion, in integers, is three times as long.)
+template <typename S>
+__device__ __forceinline__ S stored(double x) {
+    if constexpr (sizeof(S) >= 4) {
+        return S(x);
+    } else {
+        const float f = (float)x;
+        const double e = (double)f;
+        int b = __builtin_bit_cast(int, f);
+        b -= __builtin_fabs(e) > __builtin_fabs(x) ? 1 : 0;
+        b |= e != x ? 1 : 0;
+        float odd = __builtin_bit_cast(float, b);
+        asm("" : "+v"(odd));
+        return S(odd);
+    }
+}
+
+template <int D>
+struct InitCell {
+    Equilibrium<D, double, true> eq;  // deviation form, in double
+    double rho, temp, half_delta;
+
+    __device__ __forceinline__ void load(const InitFields& f, int64_t cell) {
+        rho = f.rho[cell];
+        temp = f.T[cell];
+        double u[3] = {0, 0, 0};
+#pragma unroll
+        for (int k = 0; k < D; ++k) u[k] = f.u[k * f.N + cell];
+        eq.setup(u, temp - 1.0, f.r);
+        half_delta = f.half_delta;
+    }
+    // g_i and h_i as stored, rounded once, from double
+    template <class P, int i>
+    __device__ __forceinline__ void values(const WGroups& wg, typename P::S& g,
+                                           typename P::S& h) const {
+        constexpr VelSet<D> V = kVelSet<D>;
+        constexpr Vel v = V.v[i];
+        double A0, A1, A2;  // A0 is A0 - 1 (deviation form)
+        eq.template coef<V.qn[v.group]>(A0, A1, A2);
+        const double c = eq.template dot<v.x, v.y, v.z>();
+        const double pm1 = A0 + c * (A1 + c * (A2 + c * (1.0 / 6.0 + c * (1.0 / 24.0))));
+        const double w = wg.w[v.group];
+        const double Fdev = w * (rho * pm1 + (rho - 1.0));  // F_i - w_i
+        const double hdT = half_delta * temp;
+        double gv, hv;
+        if constexpr (P::kDev) {
+            gv = Fdev;
+            hv = hdT * Fdev + half_delta * w * (temp - 1.0);  // H_i - (delta/2) w_i
+        } else {
+            gv = Fdev + w;
+            hv = hdT * (Fdev + w);
+        }
+        if constexpr (P::kScaled) {  // stored divided by w (see F16Dev)
+            gv = quotient(gv, w, wg.inv_w[v.group]);
+            hv = quotient(hv, w, wg.inv_w[v.group]);
+        }
+        g = stored<typename P::S>(gv);
+        h = stored<typename P::S>(hv);
+    }
+};
+
 }  // namespace core
 }  // namespace lbm
