@@ -282,11 +282,10 @@ int lbm_lattice(int velocity_set, int8_t *e, double *w, double *r);
  * Many independent solves -- D2Q37 and D3Q107 grids of any size, each with
  * its own gamma, tau_f, tau_g, boundary conditions and number of steps --
  * stay resident in one device arena and are advanced together: every step is
- * one launch per velocity set over all resident solves (and a run ends with
- * one tiny counter launch), and lbm_pool_run replays K such steps from a captured
- * hipGraph.  Membership lives in device tables, so solves can be admitted and
- * released between replays without re-capturing (continuous batching).  Each
- * solve follows exactly the single-solve scheme and state convention above
+ * one launch per velocity set over all resident solves, and lbm_pool_run
+ * replays K such steps and one tiny counter launch from a captured hipGraph.
+ * Membership lives in device tables, so solves can be admitted and released
+ * between replays without re-capturing (continuous batching).  Each solve follows exactly the single-solve scheme and state convention above
  * (lattice streaming, the paper's collision: the finite-difference form and
  * the energy-conserving collision are single-solve options); its arithmetic
  * does not depend on which other solves are resident.
@@ -343,7 +342,8 @@ int lbm_pool_admit_dev(lbm_pool_handle p, const lbm_request *r,
 /* Advance every resident solve that has steps left by up to `ticks` steps
  * (0..4096), asynchronously, as one replay of a captured graph (captured on
  * first use for each ticks value).  lbm_pool_run_eager enqueues the same
- * launches without a graph. */
+ * steps without a graph, each counted by itself: where a launch fails, the steps
+ * before it stand. */
 int lbm_pool_run(lbm_pool_handle p, int ticks);
 int lbm_pool_run_eager(lbm_pool_handle p, int ticks);
 

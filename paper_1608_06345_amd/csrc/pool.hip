@@ -9,9 +9,9 @@
 //   table      static per-slot parameters (geometry, physics, step budget),
 //              written by the host when membership changes.
 //   steps_done per-slot step counters, advanced on the device by k_advance
-//              once for the steps of a run (a graph replay); the host only
-//              resets a slot's counter on admission and reads them to find
-//              finished solves.
+//              once for the steps of a graph replay, after every step of a run
+//              without a graph; the host only resets a slot's counter on
+//              admission and reads them to find finished solves.
 //   directory  per velocity set: the first tile of each resident solve and
 //              its slot, in ascending tile order, plus the total tile count.
 //
@@ -132,7 +132,7 @@ void k_pool_step(const PoolArgs pa) {
 }
 
 // `ticks` steps done for every resident solve, as far as it had steps to run.
-// One launch a run: one after every step took 1.6 us of a step's time between
+// One launch a graph: one after every step took 1.6 us of a step's time between
 // the step launches (8 shock tubes 16.9 -> 15.3 us a step, 64 tubes 45.5 -> 43.9).
 __global__ __launch_bounds__(256) void k_advance(const SolveEntry* table, int64_t* steps_done,
                                                  int max_slots, int ticks) {
@@ -331,7 +331,10 @@ lbm::PoolArgs pool_args(lbm_pool* p, int d) {
     return a;
 }
 
-// Enqueue `ticks` steps for the velocity sets in `mask` (bit 0: D2Q37, bit 1: D3Q107).
+// Enqueue `ticks` steps for the velocity sets in `mask` (bit 0: D2Q37, bit 1: D3Q107),
+// counted by the one launch at their end.  A launch that fails on the way leaves the
+// steps before it uncounted: more than one of them only into a capture, which
+// is then dropped as a whole.
 int enqueue_steps(lbm_pool* p, int ticks, int mask, hipStream_t s) {
     for (int t = 0; t < ticks; ++t) {
         for (int d = 0; d < 2; ++d) {
@@ -722,7 +725,13 @@ int lbm_pool_run_eager(lbm_pool_handle p, int ticks) {
     if (rc != LBM_OK) return rc;
     const int mask = (p->resident[0] ? 1 : 0) | (p->resident[1] ? 2 : 0);
     if (!mask) return LBM_OK;
-    return enqueue_steps(p, ticks, mask, p->stream);
+    // Counted one by one: a step done and not counted is done again, from the
+    // side it did not write, but a second one would overwrite that side.
+    for (int t = 0; t < ticks; ++t) {
+        rc = enqueue_steps(p, 1, mask, p->stream);
+        if (rc != LBM_OK) return rc;
+    }
+    return LBM_OK;
 }
 
 int lbm_pool_poll(lbm_pool_handle p, int* finished, int max_finished, int* n_finished) {
