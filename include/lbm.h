@@ -289,8 +289,9 @@ int lbm_lattice(int velocity_set, int8_t *e, double *w, double *r);
  * (lattice streaming, the paper's collision: the finite-difference form and
  * the energy-conserving collision are single-solve options); its arithmetic
  * does not depend on which other solves are resident.
- * All pool memory is owned by the pool; beside the arena it holds the fields of
- * the largest solve set or read with host arrays.  A pool is not thread-safe.
+ * All pool memory is owned by the pool; beside the arena it holds, as staging,
+ * the fields of the largest solve set with host arrays or, if that is more, of
+ * the largest up to 64 MiB read with them.  A pool is not thread-safe.
  * ---------------------------------------------------------------------- */
 typedef struct lbm_pool *lbm_pool_handle;
 

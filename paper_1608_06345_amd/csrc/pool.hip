@@ -367,8 +367,8 @@ int ensure_partials(lbm_pool* p, int64_t N) {
     return LBM_OK;
 }
 
-// Staging for `need` values of initial fields or readouts (every call that
-// uses it waits for the stream before it returns).
+// Kept staging for `need` values of initial fields or readouts (every call
+// that uses it waits for the stream before it returns).
 int ensure_stage(lbm_pool* p, size_t need) {
     if (need <= p->stage_cells) return LBM_OK;
     if (p->d_stage) {
@@ -381,6 +381,28 @@ int ensure_stage(lbm_pool* p, size_t need) {
     p->stage_cells = need;
     return LBM_OK;
 }
+
+// Staging of one readout: the kept buffer where that serves it or grows to no
+// more than kKeepRead bytes, else one that is freed with the call.
+constexpr size_t kKeepRead = size_t(64) << 20;
+struct ReadStage {
+    double* d = nullptr;
+    bool own = false;
+    ~ReadStage() {
+        if (own) (void)hipFree(d);
+    }
+    int get(lbm_pool* p, size_t need) {
+        own = need > p->stage_cells && need * sizeof(double) > kKeepRead;
+        if (!own) {
+            const int rc = ensure_stage(p, need);
+            d = p->d_stage;
+            return rc;
+        }
+        const hipError_t e = hipMalloc((void**)&d, need * sizeof(double));
+        own = e == hipSuccess;
+        return lbm::err_of(e);
+    }
+};
 
 // Readout of a slot's S_n (n = its steps done), like a single solve's.
 int pool_readout(lbm_pool* p, int slot, double* rho, double* u, double* E, double* T,
@@ -766,9 +788,10 @@ int lbm_pool_moments(lbm_pool_handle p, int slot, double* rho, double* u, double
     if (!rho || !u || !E) return LBM_EINVAL;
     const Slot& sl = p->slots[slot];
     const size_t n = (size_t)sl.N * sizeof(double);
-    rc = ensure_stage(p, (size_t)sl.N * (2 + sl.dim));
+    ReadStage stage;
+    rc = stage.get(p, (size_t)sl.N * (2 + sl.dim));
     if (rc != LBM_OK) return rc;
-    double* d = p->d_stage;
+    double* d = stage.d;
     rc = pool_readout(p, slot, d, d + 2 * sl.N, d + sl.N, nullptr, false);
     hipError_t e = hipSuccess;
     if (rc == LBM_OK) e = hipMemcpyAsync(rho, d, n, hipMemcpyDeviceToHost, p->stream);
@@ -794,12 +817,13 @@ int lbm_pool_temperature(lbm_pool_handle p, int slot, double* T) {
     if (rc != LBM_OK) return rc;
     if (!T) return LBM_EINVAL;
     const size_t N = (size_t)p->slots[slot].N;
-    rc = ensure_stage(p, N);
+    ReadStage stage;
+    rc = stage.get(p, N);
     if (rc != LBM_OK) return rc;
-    rc = pool_readout(p, slot, nullptr, nullptr, nullptr, p->d_stage, false);
+    rc = pool_readout(p, slot, nullptr, nullptr, nullptr, stage.d, false);
     hipError_t e = hipSuccess;
     if (rc == LBM_OK)
-        e = hipMemcpyAsync(T, p->d_stage, N * sizeof(double), hipMemcpyDeviceToHost, p->stream);
+        e = hipMemcpyAsync(T, stage.d, N * sizeof(double), hipMemcpyDeviceToHost, p->stream);
     const hipError_t es = hipStreamSynchronize(p->stream);
     if (rc != LBM_OK) return rc;
     if (e != hipSuccess) return lbm::err_of(e);
