@@ -180,7 +180,8 @@ int lbm_set_stream(lbm_handle h, void *stream);
  *             storage, SPLIT for D3Q107 in FP64 and FP32, whose 214
  *             populations do not fit one lane's registers; finite
  *             differences: TWO_PASS, except LANE for D2Q37 in FP64 on
- *             grids under 25000 cells whose nx is not a multiple of 256.
+ *             grids of under 25000 cells, of up to four rows, and others
+ *             whose waves leave each SIMD with about one.
  * EINVAL for other values, for TWO_PASS on a lattice-streaming solve, and for
  * SPLIT_LDS on any other solve. */
 enum lbm_variant {

@@ -229,18 +229,6 @@ int lbm::solver_readout(lbm_solver* h, double* rho, double* u, double* E, double
     return readout(h, rho, u, E, T, totals);
 }
 
-namespace {
-
-// Finite differences, AUTO variant: the step from a record (fd.hip), except
-// for D2Q37 in FP64 on the smallest grids, where one fused launch is done
-// before two (1000x16, 128 kB a plane: 21.5 us fused, 22.4 in two; 256x128,
-// 262 kB: 23.6 and 22.6).
-bool fd_fused_by_default(int dim, int precision, int64_t nx, int64_t N) {
-    return dim == 2 && precision == LBM_FP64 && nx % 256 != 0 && N * 8 < 200000;
-}
-
-}  // namespace
-
 extern "C" {
 
 const char* lbm_strerror(int code) {
@@ -356,7 +344,7 @@ int create_solver(int dim, int velocity_set, double gamma, double tau_f, double 
     // across lane pairs (half storage holds them as 107 g/h words)
     h->split = lbm::default_split(dim, precision);
     h->lds = false;
-    h->fd_fused = fd_fused_by_default(dim, precision, nx, s.N);
+    h->fd_fused = lbm::fd_fused_by_default(dim, precision, nx, ny);
     hipError_t e = hipGetDevice(&h->device);
     if (e != hipSuccess) {
         delete h;
@@ -415,7 +403,7 @@ int lbm_set_variant(lbm_handle h, int variant) {
     switch (variant) {
         case LBM_VARIANT_AUTO:
             h->split = lbm::default_split(h->dim, h->precision);
-            h->fd_fused = fd_fused_by_default(h->dim, h->precision, h->nx, h->N);
+            h->fd_fused = lbm::fd_fused_by_default(h->dim, h->precision, h->nx, h->ny);
             h->lds = false;
             return LBM_OK;
         case LBM_VARIANT_LANE:

@@ -539,10 +539,10 @@ template <int D>
 constexpr int kLdsCentre = 264;
 template <int D>
 constexpr int kLdsSlots = 2 * kLdsCentre<D> + (D == 3 ? 12 : 6) * 256;
-// Populations staged per barrier phase: two for D3Q107 (2% faster at 256^3),
-// one for D2Q37, whose rows are fewer.
-template <int D>
-constexpr int kFdPhase = D == 3 ? 2 : 1;
+// Populations staged per barrier phase: two for D3Q107 in FP32 (2% faster at
+// 256^3), one otherwise (FP64 needs twice the LDS, and D2Q37 rows are fewer).
+template <int D, class P>
+constexpr int kFdPhase = (D == 3 && P::kDev) ? 2 : 1;
 
 // Stencil rows of population i staged per phase: the g and h centre rows,
 // then per moving axis (y first) and distribution the rows at -2s, -s, +s.
@@ -1183,22 +1183,23 @@ hipError_t launch_tiles(const StepArgs& a0, double* rec, hipStream_t s) {
                          src, dst, rec, a);
 }
 
-template <int D, class P, int C, bool NT>
+// LDS: the staged kernel (its 16-byte row loads need every row to start on a
+// tile boundary).
+template <int D, class P, bool LDS, bool NT, int C = 0>
 hipError_t launch_chunks(const StepArgs& a, typename P::T* rec, int grid, hipStream_t s) {
     if constexpr (C == chunk_count<D>()) {
         return hipSuccess;
     } else {
-        // rows of whole tiles in FP32: the LDS-staged kernel (its 16-byte row
-        // loads need every row to start on a tile boundary)
         constexpr int c0 = chunk_begin<D>(C), c1 = chunk_end<D>(C);
-        auto* kernel = &k_fd_update<D, P, c0, c1, NT>;
-        if constexpr (P::kDev) {
-            if (a.nx % 256 == 0) kernel = &k_fd_update_lds<D, P, c0, c1, kFdPhase<D>, NT>;
-        }
-        const hipError_t e =
-            launch_kernel(kernel, dim3(grid), dim3(256), s, a.src, a.dst, rec, a);
+        hipError_t e;
+        if constexpr (LDS)
+            e = launch_kernel(&k_fd_update_lds<D, P, c0, c1, kFdPhase<D, P>, NT>, dim3(grid),
+                              dim3(256), s, a.src, a.dst, rec, a);
+        else
+            e = launch_kernel(&k_fd_update<D, P, c0, c1, NT>, dim3(grid), dim3(256), s, a.src,
+                              a.dst, rec, a);
         if (e != hipSuccess) return e;
-        return launch_chunks<D, P, C + 1, NT>(a, rec, grid, s);
+        return launch_chunks<D, P, LDS, NT, C + 1>(a, rec, grid, s);
     }
 }
 
@@ -1207,12 +1208,55 @@ hipError_t launch_chunks(const StepArgs& a, typename P::T* rec, int grid, hipStr
 // y-2 .. y+2 of an x-chunk in 2D) is held within this much of an XCD's L2.
 constexpr int64_t kFdWindowBytes = 2 << 20;
 
-// Whether a grid of N cells (FP64) goes to k_fd_tile.  A tile's walk through
-// the planes takes 160 us (3D) or 44 us (2D) however few tiles there are; on
-// smaller grids k_fd_update is done sooner.  Both at the line (update, tiles):
-// D3Q107 40^3 (64k cells) 131 and 162 us, 48^3 (111k) 213 and 161; D2Q37 300x240
-// (72k) 38 and 45, 400^2 (160k) 75 and 47.
-bool fd_tiles(int dim, int64_t N) { return N >= (dim == 3 ? 78000 : 95000); }
+// The sweep of an update chunk's launch over the grid (sweep_tile): sets the
+// sweep fields of `a`, returns the number of workgroups.
+template <int D, typename S>
+int64_t chunk_sweep(StepArgs& a) {
+    // one x-row tile of one chunk's planes (at most 14 populations, g and h)
+    const int64_t tile_bytes = 256LL * 2 * kChunkW<D> * (int64_t)sizeof(S);
+    a.tiles_per_row = (a.nx + 255) / 256;
+    // tiles in a reuse window; D3Q107 FP64 gets twice the bytes (40^3 133 us a
+    // step, 147 without)
+    const int64_t window = (D == 3 && sizeof(S) == 8) ? 2 * kFdWindowBytes : kFdWindowBytes;
+    int64_t budget = window / (5 * tile_bytes);
+    if (budget < 1) budget = 1;
+    // x-chunks of whole rows when they fit
+    a.fd_w = (int)(a.tiles_per_row < budget ? a.tiles_per_row : budget);
+    if (D == 3) {
+        // the window is 5 slabs of YB x W tiles: the tallest sub-band within
+        // it that splits y into k rounds of eight (every XCD takes the same
+        // number of sub-bands)
+        const int64_t max_yb = budget / a.fd_w;
+        int k = 1;
+        while ((a.ny + 8 * k - 1) / (8 * k) > max_yb && 8 * k < a.ny) ++k;
+        a.fd_yb = (a.ny + 8 * k - 1) / (8 * k);
+    } else {
+        // one sub-band per XCD; the window is 5 rows of a W-tile chunk
+        a.fd_yb = (a.ny + 7) / 8;
+    }
+    const int chunks = (a.tiles_per_row + a.fd_w - 1) / a.fd_w;
+    const int subs = (a.ny + a.fd_yb - 1) / a.fd_yb;
+    const int rounds = (subs + 7) / 8;
+    return 8LL * rounds * chunks * a.fd_w * a.fd_yb * a.nz;
+}
+
+// How long such a launch is, in waves one after the other on a SIMD, times
+// four: the workgroups of a CU (32 CUs take an XCD's) times the waves of one
+// that have cells.  D2Q37 FP64 takes 8 us + 3.7 us times this a step of two
+// launches: 23 us at 4, 30 at 6, 37 at 8, 44 at 9, 52 at 12.
+int64_t chunk_load(int nx, int64_t grid) {
+    const int waves = (nx + 63) / 64;
+    return ((grid / 8 + 31) / 32) * (waves < 4 ? waves : 4);
+}
+
+// Whether a grid (FP64) goes to k_fd_tile.  A tile's walk through the planes
+// takes 160 us (3D) or 44 us (2D) however few tiles there are; on smaller grids
+// k_fd_update is done sooner.  Both at the line (update, tiles): D3Q107 40^3 (64k
+// cells) 131 and 162 us, 48^3 (111k) 213 and 161; D2Q37 2000x50 (load 8) 38
+// and 45, 65x1231 (10) 46 and 44, 1500x67 (12) 52 and 44.
+bool fd_tiles(int dim, int nx, int64_t N, int64_t grid) {
+    return dim == 3 ? N >= 78000 : chunk_load(nx, grid) >= 10;
+}
 
 template <int D, class P>
 hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, hipStream_t s) {
@@ -1225,8 +1269,9 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
                                      a.N, a.P, a.ph);
         if (e != hipSuccess) return e;
     }
+    const int64_t grid = chunk_sweep<D, typename P::S>(a);
     if constexpr (!P::kDev) {
-        if (fd_tiles(D, a.N)) {
+        if (fd_tiles(D, a.nx, a.N, grid)) {
             if constexpr (D == 3) {
                 // 64 x 8 x 4 cells, or 64 x 4 x 4 where that leaves CUs
                 // without a workgroup (1000x16x16: 281 us a step with 128 of
@@ -1240,48 +1285,53 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
             }
         }
     }
-    // one x-row tile of one chunk's planes (at most 14 populations, g and h)
-    const int64_t tile_bytes = 256LL * 2 * kChunkW<D> * (int64_t)sizeof(typename P::S);
-    a.tiles_per_row = (a.nx + 255) / 256;
-    // tiles in a reuse window; D3Q107 FP64 gets twice the bytes (3% faster
-    // at 256^3; D2Q37 FP64 was 5% slower with it, and 1.5x was slower in 3D)
-    const int64_t window = (D == 3 && sizeof(typename P::S) == 8) ? 2 * kFdWindowBytes
-                                                                   : kFdWindowBytes;
-    int64_t budget = window / (5 * tile_bytes);
-    if (budget < 1) budget = 1;
-    if (D == 3) {
-        // x-chunks of whole rows when they fit, sub-bands of YB rows: the
-        // window is 5 slabs of YB x W tiles
-        a.fd_w = (int)(a.tiles_per_row < budget ? a.tiles_per_row : budget);
-        // the tallest sub-band within the window that splits y into k
-        // rounds of eight (every XCD takes the same number of sub-bands)
-        const int64_t max_yb = budget / a.fd_w;
-        int k = 1;
-        while ((a.ny + 8 * k - 1) / (8 * k) > max_yb && 8 * k < a.ny) ++k;
-        a.fd_yb = (a.ny + 8 * k - 1) / (8 * k);
-    } else {
-        // one sub-band per XCD; the window is 5 rows of a W-tile chunk
-        a.fd_w = (int)(a.tiles_per_row < budget ? a.tiles_per_row : budget);
-        a.fd_yb = (a.ny + 7) / 8;
-    }
-    const int chunks = (a.tiles_per_row + a.fd_w - 1) / a.fd_w;
-    const int subs = (a.ny + a.fd_yb - 1) / a.fd_yb;
-    const int rounds = (subs + 7) / 8;
-    const int64_t grid = 8LL * rounds * chunks * a.fd_w * a.fd_yb * a.nz;
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     // Stores: streamed where rows are whole cache lines (elsewhere the two
     // halves of a line meet in the L2: FP32 191x173x187 5740 us a step
     // streamed, 5570 cached, 2000x30 31 and 25) and the state does not stay in
     // the caches (D2Q37 FP32 256^2, 39 MB: 23.3 and 24.0; 1024x100, 61 MB: 35.5
-    // and 27.2; D3Q107 FP32 48^3, 189 MB: 125 and 98; 64^3, 449 MB: 221 and 239)
+    // and 27.2; D3Q107 FP32 48^3, 189 MB: 125 and 98; 64^3, 449 MB: 221 and 239;
+    // D2Q37 FP64 512x48, 29 MB: 21.9 and 22.2; 1600x16, 30 MB: 26.3 and 22.4;
+    // 400x100, 47 MB: 27.5 and 22.9; D3Q107 FP64 128x8x8, 28 MB: 88 and 75)
+    constexpr int64_t least = int64_t(P::kDev ? 48 : 24) << 20;
     const int64_t state = state_bytes(D, sizeof(typename P::S), a.P);
-    const bool stays = state > (int64_t(48) << 20) && state <= (int64_t(256) << 20);
-    if (!stays && a.nx * sizeof(typename P::S) % 128 == 0)
-        return launch_chunks<D, P, 0, true>(a, rec, (int)grid, s);
-    return launch_chunks<D, P, 0, false>(a, rec, (int)grid, s);
+    const bool stays = state > least && state <= (int64_t(256) << 20);
+    const bool nt = !stays && a.nx * sizeof(typename P::S) % 128 == 0;
+    if (a.nx % 256 == 0) {
+        if constexpr (P::kDev) {
+            return nt ? launch_chunks<D, P, true, true>(a, rec, (int)grid, s)
+                      : launch_chunks<D, P, true, false>(a, rec, (int)grid, s);
+        }
+    }
+    return nt ? launch_chunks<D, P, false, true>(a, rec, (int)grid, s)
+              : launch_chunks<D, P, false, false>(a, rec, (int)grid, s);
 }
 
 }  // namespace
+
+// D2Q37 in FP64 only (D3Q107 FP64 48x13x11: 80 us from the record; 64^3 and up two
+// to four times as long fused).  us a step, fused / chunks / tiles:
+//   small grids, where one launch is done before two: 1000x16 21 / 23 / 44, 2000x12
+//   21 / 22, 300x80 23 / 22;
+//   up to four rows: three of a tile's four waves have no cells, and the chunks,
+//   dealt to the XCDs by rows, leave half of them idle: 40000x3 47 / 84 / 94,
+//   100000x1 41 / 196 / 198, 1000000x3 1350 / 2550 / 1680 (40000x6: 104 / 124 / 96);
+//   up to one wave a SIMD (1024 of 64 cells of a row), with more than one of
+//   the chunks': 300x133 25 / 37 / 44, 150x267 24 / 30 / 44 (500x128, one of the
+//   chunks': 33 / 24);
+//   and up to two, where the tiles are more than the CUs: 25600x4 46 / 73 / 59.
+bool fd_fused_by_default(int dim, int precision, int64_t nx, int64_t ny) {
+    if (dim != 2 || precision != LBM_FP64) return false;
+    if (nx * ny < 25000 || ny <= 4) return true;
+    StepArgs a{};
+    a.nx = (int32_t)nx;
+    a.ny = (int32_t)ny;
+    a.nz = 1;
+    const int64_t load = chunk_load(a.nx, chunk_sweep<2, double>(a));
+    const int64_t cols = (nx + 63) / 64, waves = cols * ny, tiles = cols * ((ny + 15) / 16);
+    if (load >= 10) return waves <= 2048 && tiles > 256;
+    return waves <= 1024 && load > 4;
+}
 
 size_t fd_record_bytes(int dim, int precision, int64_t P) {
     const bool dev = precision != LBM_FP64;  // record (deviation storage: residuals too)

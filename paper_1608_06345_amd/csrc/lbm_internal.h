@@ -217,6 +217,8 @@ hipError_t launch_fd_step(int dim, int precision, bool split, const StepArgs& a,
 // record, then update passes over chunks of populations, which also leave
 // the next step's record behind (record_valid: skip the moments pass).
 // FP64 and FP32 deviation storage.
+// Whether AUTO takes the fused step instead (launch_fd_step, one lane per cell).
+bool fd_fused_by_default(int dim, int precision, int64_t nx, int64_t ny);
 size_t fd_record_bytes(int dim, int precision, int64_t P);
 // S_0 of the finite-difference form and, unless `record` is null, its record.
 hipError_t launch_fd_init(int dim, int precision, void* dst, void* record, const InitFields& f,
