@@ -1216,7 +1216,7 @@ int64_t chunk_sweep(StepArgs& a) {
     const int64_t tile_bytes = 256LL * 2 * kChunkW<D> * (int64_t)sizeof(S);
     a.tiles_per_row = (a.nx + 255) / 256;
     // tiles in a reuse window; D3Q107 FP64 gets twice the bytes (40^3 133 us a
-    // step, 147 without)
+    // step, 147 without; 1100x1100x1 2050 and 2430)
     const int64_t window = (D == 3 && sizeof(S) == 8) ? 2 * kFdWindowBytes : kFdWindowBytes;
     int64_t budget = window / (5 * tile_bytes);
     if (budget < 1) budget = 1;
@@ -1253,9 +1253,11 @@ int64_t chunk_load(int nx, int64_t grid) {
 // takes 160 us (3D) or 44 us (2D) however few tiles there are; on smaller grids
 // k_fd_update is done sooner.  Both at the line (update, tiles): D3Q107 40^3 (64k
 // cells) 131 and 162 us, 48^3 (111k) 213 and 161; D2Q37 2000x50 (load 8) 38
-// and 45, 65x1231 (10) 46 and 44, 1500x67 (12) 52 and 44.
-bool fd_tiles(int dim, int nx, int64_t N, int64_t grid) {
-    return dim == 3 ? N >= 78000 : chunk_load(nx, grid) >= 10;
+// and 45, 65x1231 (10) 46 and 44, 1500x67 (12) 52 and 44.  In 3D with one plane in z
+// a tile is a quarter full at best: 300x300x1 257 and 473, 1100x1100x1 2060 and
+// 2650, but 300x300x3 650 and 485, 600x600x2 1220 and 900.
+bool fd_tiles(int dim, int nx, int nz, int64_t N, int64_t grid) {
+    return dim == 3 ? N >= 78000 && nz > 1 : chunk_load(nx, grid) >= 10;
 }
 
 template <int D, class P>
@@ -1271,7 +1273,7 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
     }
     const int64_t grid = chunk_sweep<D, typename P::S>(a);
     if constexpr (!P::kDev) {
-        if (fd_tiles(D, a.nx, a.N, grid)) {
+        if (fd_tiles(D, a.nx, a.nz, a.N, grid)) {
             if constexpr (D == 3) {
                 // 64 x 8 x 4 cells, or 64 x 4 x 4 where that leaves CUs
                 // without a workgroup (1000x16x16: 281 us a step with 128 of
@@ -1301,6 +1303,12 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
         if constexpr (P::kDev) {
             return nt ? launch_chunks<D, P, true, true>(a, rec, (int)grid, s)
                       : launch_chunks<D, P, true, false>(a, rec, (int)grid, s);
+        } else if constexpr (D == 3) {
+            // one plane in z, and grids just short of the tiles (256x16x17: 133 us
+            // staged, 143 not; 256x16x16, a workgroup a CU: 121 and 100;
+            // 256x400x1 146 and 187, 1024x1024x1 1147 and 1540)
+            if (chunk_load(a.nx, grid) > 4)
+                return launch_chunks<D, P, true, true>(a, rec, (int)grid, s);
         }
     }
     return nt ? launch_chunks<D, P, false, true>(a, rec, (int)grid, s)

@@ -46,3 +46,15 @@ def test_2d_fp64(tmp_path):
         # cached stores (NT = false) of a state that fits the caches
         grid(400, 100, CHUNKS, "Lb0E"), grid(2000, 20, CHUNKS, "Lb0E"),
     ], tmp_path)
+
+
+def test_3d_fp64(tmp_path):
+    grid = lambda *a: (3, a[:3], AUTO, *a[3:])
+    _check([
+        # one plane in z fills a tile to a quarter
+        grid(300, 300, 1, CHUNKS), grid(1000, 100, 1, CHUNKS), grid(300, 300, 2, TILES),
+        grid(300, 1, 300, TILES), grid(40, 45, 45, TILES),
+        # rows of whole 256 cells, more than a workgroup a CU: staged
+        grid(256, 400, 1, STAGED), grid(1024, 100, 1, STAGED), grid(256, 16, 17, STAGED),
+        grid(256, 16, 16, CHUNKS), grid(256, 17, 18, TILES),
+    ], tmp_path)
