@@ -1275,12 +1275,13 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
     if constexpr (!P::kDev) {
         if (fd_tiles(D, a.nx, a.nz, a.N, grid)) {
             if constexpr (D == 3) {
-                // 64 x 8 x 4 cells, or 64 x 4 x 4 where that leaves CUs
-                // without a workgroup (1000x16x16: 281 us a step with 128 of
-                // the larger, 188 with 256 of the smaller)
-                const int64_t tiles8 = (int64_t)((a.nx + 63) / 64) * ((a.ny + 7) / 8) *
+                // 64 x 8 x 4 cells, or 64 x 4 x 4 where no CU gets two of those
+                // (1000x16x16: 279 us a step with 128 of the larger, 185 with
+                // 256 of the smaller; 300x300x2 450 with 190, 480 with 375) and
+                // where the larger have no more rows to serve (20000x2x2 440, 316)
+                const int64_t tiles4 = (int64_t)((a.nx + 63) / 64) * ((a.ny + 3) / 4) *
                                        ((a.nz + kTileZ - 1) / kTileZ);
-                if (tiles8 < 256) return launch_tiles<D, 4>(a, rec, s);
+                if (tiles4 <= 256 || a.ny <= 4) return launch_tiles<D, 4>(a, rec, s);
                 return launch_tiles<D, 8>(a, rec, s);
             } else {
                 return launch_tiles<D, 4>(a, rec, s);

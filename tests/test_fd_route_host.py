@@ -58,3 +58,13 @@ def test_3d_fp64(tmp_path):
         grid(256, 400, 1, STAGED), grid(1024, 100, 1, STAGED), grid(256, 16, 17, STAGED),
         grid(256, 16, 16, CHUNKS), grid(256, 17, 18, TILES),
     ], tmp_path)
+
+
+def test_tile_height_3d_fp64(tmp_path):
+    grid = lambda *a: (3, a[:3], AUTO, TILES, a[3])
+    low, high = "ILi3ELi4E", "ILi3ELi8E"
+    _check([
+        grid(64, 64, 64, low), grid(1000, 16, 16, low),  # no CU gets two
+        grid(65, 48, 48, high), grid(300, 300, 2, high), grid(128, 128, 64, high),
+        grid(20000, 2, 2, low), grid(300, 4, 300, low),  # no more rows than four
+    ], tmp_path)
