@@ -50,3 +50,46 @@ def _compare(dim, shape, bc, steps, energy=False):
 @pytest.mark.parametrize("energy", [False, True])
 def test_staged_chunks(shape, bc, energy):
     _compare(3, shape, bc, 5, energy)
+
+
+@pytest.mark.parametrize("shape,bc", [
+    ((64, 35, 37), lbm.LBM_BC(PER, OPEN, PER)),    # 64 x 4 x 4, streamed
+    ((64, 70, 58), lbm.LBM_BC(PER, PER, OPEN)),    # 64 x 8 x 4, streamed
+    ((80, 66, 61), lbm.LBM_BC(OPEN, PER, PER)),    # the same, ragged along every axis
+    ((176, 150, 3), lbm.LBM_BC(PER, PER, OPEN)),   # columns of three and two planes
+    ((200, 200, 2), 0),
+    ((400, 2, 100), lbm.LBM_BC(PER, OPEN, PER)),   # one to three rows
+    ((333, 3, 80), 0),
+    ((1000, 1, 79), 0),
+    ((2, 300, 140), lbm.LBM_BC(PER, PER, OPEN)),   # two and three cells
+    ((3, 300, 90), 0),
+    ((43, 48, 39), 0),                             # odd rows, cells a multiple of 16
+])
+def test_tiles_3d(shape, bc):
+    _compare(3, shape, bc, 5)
+
+
+@pytest.mark.parametrize("shape,bc", [
+    ((1008, 130, 1), 0),                           # streamed, ragged along y
+    ((1024, 160, 1), lbm.LBM_BC(OPEN, OPEN)),      # streamed, whole tiles
+    ((703, 275, 1), lbm.LBM_BC(PER, OPEN)),
+    ((703, 272, 1), 0),                            # odd rows, cells a multiple of 16
+    ((64000, 3, 1), lbm.LBM_BC(OPEN, OPEN)),
+    ((64000, 3, 1), 0),
+    ((32768, 2, 1), lbm.LBM_BC(PER, OPEN)),
+    ((90000, 1, 1), 0),
+    ((2, 5000, 1), lbm.LBM_BC(PER, OPEN)),
+    ((3, 64001, 1), 0),
+])
+def test_tiles_2d(shape, bc):
+    _compare(2, shape, bc, 5)
+
+
+@pytest.mark.parametrize("dim,shape", [(2, (703, 275, 1)), (2, (1008, 130, 1)), (3, (64, 70, 58))])
+def test_tiles_energy_conserving(dim, shape):
+    _compare(dim, shape, 0, 5, energy=True)
+
+
+@pytest.mark.parametrize("dim,shape,steps", [(2, (48, 2401, 1), 300), (3, (64, 33, 38), 100)])
+def test_tiles_many_steps(dim, shape, steps):
+    _compare(dim, shape, 0, steps)
