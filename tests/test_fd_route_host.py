@@ -68,3 +68,15 @@ def test_tile_height_3d_fp64(tmp_path):
         grid(65, 48, 48, high), grid(300, 300, 2, high), grid(128, 128, 64, high),
         grid(20000, 2, 2, low), grid(300, 4, 300, low),  # no more rows than four
     ], tmp_path)
+
+
+def test_accuracy_samples_run_the_timed_kernels(tmp_path):
+    """The benchmark prints an error on a small grid beside a rate on a large
+    one: both have to come from the same kernels."""
+    import bench
+    for dim, large in ((2, (4096, 4096, 1)), (3, (256, 256, 256))):
+        small = bench.ACCURACY_SAMPLES["fd", dim][0]
+        for precision in ("LBM_FP64", "LBM_FP32_DEV"):
+            code = _ROUTE.replace("dt=0.06", "dt=0.06, precision=lbm." + precision)
+            a, b = run(code.format(cases=[(dim, small, AUTO), (dim, large, AUTO)]), tmp_path)
+            assert a == b and a, (dim, precision)
