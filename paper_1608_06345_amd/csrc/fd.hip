@@ -496,8 +496,8 @@ __global__ __launch_bounds__(256) void k_fd_update(const void* __restrict__ src_
     if (cx >= a.nx) return;
     const int64_t cell = (int64_t)cx + (int64_t)a.nx * cy + (int64_t)a.nxy * cz;
     const Physics& ph = a.ph;
-    PullTable<D> pt;  // pt.src for shift e gives the cell at x - e (wrapped or clamped)
-    pt.fill(cx, cy, cz, a.nx, a.ny, a.nz, a.nxy, a.open_end, true);
+    PullTable<D> pt;  // entry e + 3: the coordinate x - e (wrapped or clamped)
+    pt.fill(cx, cy, cz, a.nx, a.ny, a.nz, a.nxy, a.open_end);
     const S* src = static_cast<const S*>(src_v);
     S* dst = static_cast<S*>(dst_v);
     FdCell<D, P, C0, C1> c;

@@ -1,6 +1,6 @@
 // HIP kernels for gfx950: initialisation, the fused collide-and-stream step,
-// the fused finite-difference step (Sec. III; its two-pass form is in
-// fd.hip), and the FP64 readout / conservation reductions.
+// the fused finite-difference step (Sec. III; the one that works from a record
+// is in fd.hip), and the FP64 readout / conservation reductions.
 //
 // Data layout in HBM (one ping-pong side): population i owns a slab of 2 P
 // values (P >= N, x fastest).  FP64 and FP32: the g plane, then the h plane
@@ -45,7 +45,7 @@ using namespace core;
 // y and z offsets have moved from scalar to vector registers.)  The
 // hardware deals workgroups to the eight XCDs round-robin by id: workgroup b
 // is turn j = b / 8 of XCD b % 8.  The turns of one XCD walk runs of a.run
-// consecutive tiles (four waves each; about one row), so that the cache lines
+// consecutive tiles (a.waves waves each; about one row), so that the cache lines
 // that x-shifted pulls share between neighbouring waves are fetched into one
 // L2 once, while the eight XCDs together still sweep one compact band of
 // rows.
@@ -317,7 +317,7 @@ __device__ __forceinline__ bool fd_item(const StepArgs& a, int lane_cell, uint32
     z = __builtin_amdgcn_readfirstlane(z);
     const int xr = seg * L + lane_cell;
     const int x = xr < a.nx ? xr : a.nx - 1;  // tail lanes repeat the last cell
-    fill_row_offsets<D, S>(o, x, y, z, a.nx, a.ny, a.nz, a.nxy, a.open_end, true, role_off);
+    fill_row_offsets<D, S>(o, x, y, z, a.nx, a.ny, a.nz, a.nxy, a.open_end, role_off);
     return true;
 }
 

@@ -65,21 +65,14 @@ template <int D>
 struct PullTable {
     int x[7], y[7], z[7];
     __device__ __forceinline__ void fill(int cx, int cy, int cz, int nx, int ny,
-                                         int nz, int nxy, uint32_t open_end,
-                                         bool stream) {
+                                         int nz, int nxy, uint32_t open_end) {
 #pragma unroll
         for (int k = 0; k < 7; ++k) {
-            const int e = stream ? k - 3 : 0;
+            const int e = k - 3;
             x[k] = pull_coord(cx, e, nx, open_end & 1u);
             y[k] = pull_coord(cy, e, ny, open_end & 2u) * nx;
             if constexpr (D == 3) z[k] = pull_coord(cz, e, nz, open_end & 4u) * nxy;
         }
-    }
-    // source cell of the population with lattice vector (EX, EY, EZ)
-    template <int EX, int EY, int EZ>
-    __device__ __forceinline__ int src() const {
-        if constexpr (D == 3) return x[EX + 3] + y[EY + 3] + z[EZ + 3];
-        else return x[EX + 3] + y[EY + 3];
     }
 };
 
@@ -491,16 +484,15 @@ struct RowOffsets {
     uint32_t row;    // wave-uniform: byte offset of the row start
 };
 
-// Fill the offsets for the lane's cell x of row (y, z); `stream` = false
-// points every pull at the cell itself (collision without streaming).
+// Fill the offsets for the lane's cell x of row (y, z).
 template <int D, typename T>
 __device__ __forceinline__ void fill_row_offsets(RowOffsets<T>& o, int x, int y, int z, int nx,
                                                  int ny, int nz, int nxy, uint32_t open_end,
-                                                 bool stream, uint32_t role_off) {
+                                                 uint32_t role_off) {
     constexpr uint32_t cb = cell_bytes(sizeof(T));
 #pragma unroll
     for (int k = 0; k < 7; ++k) {
-        const int e = stream ? k - 3 : 0;
+        const int e = k - 3;
         o.xo[k] = (uint32_t)pull_coord(x, e, nx, open_end & 1u) * cb + role_off;
         o.yo[k] = (uint32_t)(pull_coord(y, e, ny, open_end & 2u) * nx) * cb;
         if constexpr (D == 3)
