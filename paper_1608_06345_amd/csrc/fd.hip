@@ -918,9 +918,11 @@ void k_fd_tile(const double* __restrict__ src, double* __restrict__ dst,
     // the column's cells in memory
     const bool active = x0 + lane < a.nx && (D == 2 || y0 + wave < a.ny);
     const uint32_t xo = (uint32_t)(x0 + lane) * S;
-    const uint32_t v_cell = active ? (uint32_t)(D == 3 ? (y0 + wave) * a.nx + m0 * a.nxy
-                                                       : m0 * a.nx) * S + xo
-                                   : kNone;
+    // (unsigned: a column past the end of a few long rows may wrap; it stores nothing)
+    const uint32_t first = D == 3 ? (uint32_t)(y0 + wave) * (uint32_t)a.nx +
+                                        (uint32_t)m0 * (uint32_t)a.nxy
+                                  : (uint32_t)m0 * (uint32_t)a.nx;
+    const uint32_t v_cell = active ? first * S + xo : kNone;
     // row k of the column in a plane; rows past the grid: an empty one
     auto row_rsrc = [&](const double* plane, int k) {
         return plane_rsrc(plane, m0 + k < nm ? (uint32_t)a.P * S : 0u);
