@@ -360,10 +360,11 @@ def _gpu_sample(p, shape, steps, store=None, fields=None):
 
 
 # Same-recipe samples for the per-path error against the oracle: small
-# enough for the host, on the kernels of the timed grids (rows of whole LDS tiles, 128
-# cells for the staged pull, 256 for the FP32 finite differences; in FP64 finite
-# differences enough cells for the tiles, 64 x 8 x 4 in 3D; in FP32 for streamed stores), and for 3D few enough
-# steps that seed 3's velocity modes are still alive (max |u| ~1e-2).
+# enough for the host, rows of whole LDS tiles (128 cells for the staged pull, 256
+# for the FP32 finite differences), finite differences on the kernels of the timed
+# grids (FP64: enough cells for the tiles, 64 x 8 x 4 in 3D; FP32: for streamed
+# stores), and for 3D few enough steps that seed 3's velocity modes are still alive
+# (max |u| ~1e-2).
 ACCURACY_SAMPLES = {
     ("lattice", 3): ((128, 64, 64), 30),
     ("lattice", 2): ((256, 256, 1), 300),

@@ -168,9 +168,10 @@ int lbm_set_stream(lbm_handle h, void *stream);
  *             lane l + 32 of the wave;
  *   TWO_PASS  (lbm_create_fd solves only) the finite-difference step as a
  *             per-cell record of the macroscopic state and updates of the
- *             populations from it: in FP64 on grids of some size one launch
- *             that walks tiles of cells through all planes in LDS, else a
- *             launch per chunk of populations (same results to rounding);
+ *             populations from it: in FP64 on grids of some size (in 3D of
+ *             more than one plane) one launch that walks tiles of cells
+ *             through all planes in LDS, else a launch per chunk of
+ *             populations (same results to rounding);
  *   SPLIT_LDS (D3Q107 lattice streaming, nx a multiple of 128) SPLIT with
  *             the pulled rows staged in LDS: a workgroup loads each
  *             population's shifted row once, four cells a lane, and each

@@ -13,16 +13,19 @@
 //                tile of cells through all planes, each plane's tile and its
 //                stencil's halo in LDS; the new populations' moment sums stay
 //                in registers and become the next record.  One launch a step.
-//   k_fd_update  FP32, and FP64 on small grids: one lane per cell, a chunk of
-//                populations per launch, neighbours read through L1/L2, the
-//                moment sums passed on from chunk to chunk in memory.  It has
-//                more waves, each with a shorter chain of planes.  In FP32
-//                with rows of whole 256-cell tiles, k_fd_update_lds instead,
+//   k_fd_update  FP32, and FP64 on small grids and those of one plane: one lane
+//                per cell, a chunk of populations per launch, neighbours read
+//                through L1/L2, the moment sums passed on from chunk to chunk
+//                in memory.  It has more waves, each with a shorter chain of
+//                planes.  With rows of whole 256-cell tiles in FP32, and in 3D
+//                FP64 with more than a workgroup a CU, k_fd_update_lds instead,
 //                which stages each population's stencil rows in LDS.
 //
-// (FP32 in tiles sums in another order.  At 256^3 that took 6.4 ms against
-// 10.2 a step, but moved the deviations' last bits: the velocity's error
-// against FP64 after six steps 2.6e-7 to 2.3e-7.  It keeps the chunks.)
+// (FP32 keeps the chunks' order of sums.  k_fd_tile sums pairs, from the last
+// population to the first; FP32 in such tiles took 6.4 ms against 10.2 a step at
+// 256^3, but moved the deviations' last bits: the velocity's error against FP64
+// after six steps 2.6e-7, 2.3e-7 in chunks.  Tiles that walk the populations in
+// the chunks' order and keep their partial sums are not built.)
 //
 // The first record is made with the initial state (k_fd_init), and from the
 // populations (k_fd_moments) only after a fused step.
@@ -717,9 +720,10 @@ __global__ __launch_bounds__(256) void k_fd_update_lds(const void* __restrict__ 
 // ahead, they took 7.5, 1.50, 4.1 and 0.53: direct loads into LDS free those
 // registers and carry the loads three planes ahead.  A tile of 64 x 8 x 4 cells
 // asks the L2 for 1.9 cells per cell (64 x 4 x 4: 2.2, 5% slower), part of the
-// halo is found there, and HBM reads come to about 1.6 times the populations
-// in 3D, 1.2 in 2D.  That traffic bounds it: 5.6-6 TB/s with the writes.  Two
-// cells a lane (64 x 8 x 2) took 6.6 ms and 3.7 in 2D, eight spilled.
+// halo is found there, and HBM reads come to 1.44 times the populations in 3D
+// (256^3), 1.21 in 2D (4096^2).  That traffic bounds it: with the writes 5.6 TB/s
+// and 6.2.  Two cells a lane (64 x 8 x 2) took 6.6 ms and 3.7 in 2D, eight
+// spilled.
 constexpr int kTileZ = 4;
 
 template <int D, int TY>

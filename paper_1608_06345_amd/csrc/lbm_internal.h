@@ -213,10 +213,10 @@ hipError_t launch_step(int dim, int precision, bool split, const StepArgs& a,
 // fields of a copy of `a`.
 hipError_t launch_fd_step(int dim, int precision, bool split, const StepArgs& a,
                           hipStream_t s);
-// The same step in two passes (fd.hip): a moments pass writing a per-cell
-// record, then update passes over chunks of populations, which also leave
-// the next step's record behind (record_valid: skip the moments pass).
-// FP64 and FP32 deviation storage.
+// The same step from a per-cell record of the macroscopic state (fd.hip):
+// every population's update also adds to the next step's record
+// (record_valid: the record is that of a.src; otherwise a moments pass makes it
+// first).  FP64 and FP32 deviation storage.
 // Whether AUTO takes the fused step instead (launch_fd_step, one lane per cell).
 bool fd_fused_by_default(int dim, int precision, int64_t nx, int64_t ny);
 size_t fd_record_bytes(int dim, int precision, int64_t P);
@@ -296,7 +296,7 @@ struct lbm_solver {
     bool split;
     bool lds;             // D3Q107 lattice step: pulled rows staged in LDS
     bool fd_fused;        // finite differences: one fused kernel (LANE / SPLIT variants)
-    void* fd_record;      // finite differences, two passes: per-cell record
+    void* fd_record;      // finite differences: per-cell record (TWO_PASS)
     bool fd_record_valid; // the record describes the current state
     lbm::HostStage stage; // fields of host-array calls
     size_t device_bytes;

@@ -37,8 +37,9 @@ def _compare(dim, shape, bc, steps, energy=False):
         s.step(steps)
         g = s.moments()
         T = s.temperature()
-    assert_close((g[0], g[1], T), (rho, u, o.temperature(u, E)), TOL_FP64,
-                 f"FD FP64 {shape} bc={bc} {steps} steps")
+    e = assert_close((g[0], g[1], T), (rho, u, o.temperature(u, E)), TOL_FP64,
+                     f"FD FP64 {shape} bc={bc} {steps} steps")
+    print(f"\nPARITY FD FP64 {shape} bc={bc} {steps} steps energy={energy} rho/u/T={e}")
 
 
 @pytest.mark.parametrize("shape,bc", [
