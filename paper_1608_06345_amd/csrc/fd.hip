@@ -1262,8 +1262,10 @@ int64_t chunk_load(int nx, int64_t grid) {
 // and 45, 65x1231 (10) 46 and 44, 1500x67 (12) 52 and 44.  In 3D with one plane in z
 // a tile is a quarter full at best: 300x300x1 257 and 473, 1100x1100x1 2060 and
 // 2650, but 300x300x3 650 and 485, 600x600x2 1220 and 900.
-bool fd_tiles(int dim, int nx, int nz, int64_t N, int64_t grid) {
-    return dim == 3 ? N >= 78000 && nz > 1 : chunk_load(nx, grid) >= 10;
+template <int D>
+bool fd_tiles(StepArgs a) {
+    if constexpr (D == 3) return a.N >= 78000 && a.nz > 1;
+    else return chunk_load(a.nx, chunk_sweep<2, double>(a)) >= 10;
 }
 
 template <int D, class P>
@@ -1277,9 +1279,8 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
                                      a.N, a.P, a.ph);
         if (e != hipSuccess) return e;
     }
-    const int64_t grid = chunk_sweep<D, typename P::S>(a);
     if constexpr (!P::kDev) {
-        if (fd_tiles(D, a.nx, a.nz, a.N, grid)) {
+        if (fd_tiles<D>(a)) {
             if constexpr (D == 3) {
                 // 64 x 8 x 4 cells, or 64 x 4 x 4 where no CU gets two of those
                 // (1000x16x16: 279 us a step with 128 of the larger, 185 with
@@ -1294,6 +1295,7 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
             }
         }
     }
+    const int64_t grid = chunk_sweep<D, typename P::S>(a);
     if (grid > 0x7fffffff) return hipErrorInvalidValue;
     // Stores: streamed where rows are whole cache lines (elsewhere the two
     // halves of a line meet in the L2: FP32 191x173x187 5740 us a step
@@ -1334,7 +1336,8 @@ hipError_t fd_two_pass_impl(const StepArgs& a0, void* rec_v, bool record_valid, 
 //   up to one wave a SIMD (1024 of 64 cells of a row), with more than one of
 //   the chunks': 300x133 25 / 37 / 44, 150x267 24 / 30 / 44 (500x128, one of the
 //   chunks': 33 / 24);
-//   and up to two, where the tiles are more than the CUs: 25600x4 46 / 73 / 59.
+//   and up to two, where the tiles are more than the CUs: 16400x5 42 fused, 57 in
+//   tiles, 24000x5 54 and 59.
 bool fd_fused_by_default(int dim, int precision, int64_t nx, int64_t ny) {
     if (dim != 2 || precision != LBM_FP64) return false;
     if (nx * ny < 25000 || ny <= 4) return true;

@@ -467,11 +467,11 @@ __global__ __launch_bounds__(256) void k_final_reduce(const double* __restrict__
 template <int D, class P>
 constexpr int kSplitWaves = (D == 3 && sizeof(typename P::T) == 4) ? 2 : 1;
 
-// Stores of a step (streamed / cached, us): D2Q37 FP32 512^2 (155 MB) 33.0 /
-// 25.1, 700^2 (290 MB) 57.0 / 53.0, FP16 1024^2 (310 MB) 70.6 / 66.9, D3Q107
-// FP32 45x40x40 (123 MB) 30.8 / 25.3; beyond, D3Q107 FP32 64^3 (449 MB)
-// 87.0 / 88.8, 256^3 5149 / 5715; below, FP32 32^3 (56 MB) 13.4 / 14.3, D2Q37
-// 256^2 (39 MB) 11.5 / 11.9.
+// Stores of a step (streamed / cached, us, on one allocation in turn): D2Q37 FP32
+// 512^2 (155 MB) 32.6 / 26.2, 700^2 (290 MB) 57.0 / 54.5, FP16 1024^2 (310 MB)
+// 63.6 / 59.7, D3Q107 FP32 45x40x40 (123 MB) 31.1 / 25.4; beyond, D3Q107 FP32 64^3
+// (449 MB) 87.8 / 90.3, 256^3 5552 / 5654 (more apart on some allocations); below,
+// FP32 32^3 (56 MB) 13.6 / 14.3, D2Q37 256^2 (39 MB) 12.1 / 12.8.
 bool streamed(int dim, size_t elem, int64_t P) {
     const int64_t state = state_bytes(dim, elem, P);
     return state <= (int64_t(64) << 20) || state > (int64_t(304) << 20);
