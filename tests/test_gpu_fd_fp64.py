@@ -74,6 +74,7 @@ def test_tiles_3d(shape, bc):
     ((1008, 130, 1), 0),                           # streamed, ragged along y
     ((1024, 160, 1), lbm.LBM_BC(OPEN, OPEN)),      # streamed, whole tiles
     ((703, 275, 1), lbm.LBM_BC(PER, OPEN)),
+    ((1999, 80, 1), lbm.LBM_BC(OPEN, PER)),
     ((703, 272, 1), 0),                            # odd rows, cells a multiple of 16
     ((64000, 3, 1), lbm.LBM_BC(OPEN, OPEN)),
     ((64000, 3, 1), 0),
