@@ -19,7 +19,7 @@ ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 def core(tmp_path_factory):
     so = str(tmp_path_factory.mktemp("core") / "libhostcore.so")
     subprocess.check_call(
-        ["/opt/rocm/llvm/bin/clang++", "-x", "c++", "-std=c++20", "-O1", "-march=x86-64-v3", "-w",
+        ["/opt/rocm/llvm/bin/clang++", "-x", "c++", "-std=c++20", "-O1", "-w",
          "-ffp-contract=off", "-shared", "-fPIC", "-D__HIP_PLATFORM_AMD__", "-I/opt/rocm/include",
          "-I" + os.path.join(ROOT, "include"),
          "-I" + os.path.join(ROOT, "paper_1608_06345_amd", "csrc"),
